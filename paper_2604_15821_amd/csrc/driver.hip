@@ -206,6 +206,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   const int Ef = p.Ef, kf = p.kf, hf = p.hdf;
   if (atom) hipLaunchKernelGGL(iota_kernel, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, p.iota, N);
   const bool attn = p.attn != 0;
+  // Split products (half the error of the fp32 matrix instructions and up to twice their rate)
+  // for every model but those with attention: there the weight gradient amplifies any change of
+  // rounding (the step of 64 cells with 4 heads lies 2e-6 to 3e-3 from the 64-bit result,
+  // depending on the batch, with either product), so its results are kept bit for bit.
+  const bool split = !attn;
   const int H = p.H;
   // head width: the register-resident kernels (heads of 32 columns, neighbourhoods of
   // up to kAttnMfmaN edges) and the tiled sweeps beside them; wider heads take the
@@ -452,12 +457,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<false>(st, LoadPlain{Z3s(t), d}, Wp(blk(t, "W1a")), d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<false>(split, st, LoadPlain{Z3s(t), d}, Wp(blk(t, "W1a")), d, h3, TL3(t), p.ntiles3 + t, p.mt3,
                            EpiStore{A3(t), h3});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<false>(st, LoadSilu{A3(t), h3}, Wp(blk(t, "W2a")), h3, d, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<false>(split, st, LoadSilu{A3(t), h3}, Wp(blk(t, "W2a")), h3, d, TL3(t), p.ntiles3 + t, p.mt3,
                            EpiRowScale{p.T3a, SG3(t), d});
       }
       {
@@ -477,7 +482,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_ROUTE, 2.0 * Ne * d * Ep, Ne * (4.0 * d + 4.0 * Ep));
-        launch_rows<false>(st, LoadPlain{XeR(t), d}, WRP(t), d, (int)Ep, p.tilesE, p.ntE, p.mtE,
+        launch_rows<false>(split, st, LoadPlain{XeR(t), d}, WRP(t), d, (int)Ep, p.tilesE, p.ntE, p.mtE,
                            EpiStore{p.Lw, Ep});
         float* gap = dbg && dbg->gap ? dbg->gap + t * ca.Ne_tot + ca.e0 : nullptr;
         if (Ne > 0)
@@ -501,14 +506,14 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     }
     {
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<false>(st, LoadPlain{Xs(t), d}, W1, d, h, TL(t), p.ntiles + t, p.mt, EpiStore{Aa(t), h});
+      launch_rows<false>(split, st, LoadPlain{Xs(t), d}, W1, d, h, TL(t), p.ntiles + t, p.mt, EpiStore{Aa(t), h});
     }
     {
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
       if (p.rf)   // expert outputs before gating (the gates' adjoints need them)
-        launch_rows<false>(st, LoadSilu{Aa(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{YstR(t), d});
+        launch_rows<false>(split, st, LoadSilu{Aa(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{YstR(t), d});
       else
-        launch_rows<false>(st, LoadSilu{Aa(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiRowScale{p.T1, SG(t), d});
+        launch_rows<false>(split, st, LoadSilu{Aa(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiRowScale{p.T1, SG(t), d});
     }
     // u = h + messages (h^{t+1} itself without the feature-update MoE)
     float* u_out = atom ? p.ut : HV(p.h, t + 1);
@@ -524,7 +529,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_DENSE_GEMM, f_qkv, 0);
-        launch_rows<false>(st, LoadPlain{MM(t), d}, Wp(blk(t, "Wqkv")), d, 3 * d, p.tilesE, p.ntE, p.mtE,
+        launch_rows<false>(kFp32, st, LoadPlain{MM(t), d}, Wp(blk(t, "Wqkv")), d, 3 * d, p.tilesE, p.ntE, p.mtE,
                            EpiStore{QKVt(t), 3LL * d});
       }
       {
@@ -548,7 +553,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_DENSE_GEMM, f_dense, 0);
-        launch_rows<false>(st, LoadPlain{OSt(t), d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
+        launch_rows<false>(kFp32, st, LoadPlain{OSt(t), d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
                            EpiAdd{u_out, HV(p.h, t), d});
       }
     } else if (p.rf) {
@@ -571,11 +576,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<false>(st, LoadPlain{Xsf(t), d}, W1f, d, hf, TLF(t), p.ntilesf + t, p.mtf, EpiStore{Af(t), hf});
+        launch_rows<false>(split, st, LoadPlain{Xsf(t), d}, W1f, d, hf, TLF(t), p.ntilesf + t, p.mtf, EpiStore{Af(t), hf});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<false>(st, LoadSilu{Af(t), hf}, W2f, hf, d, TLF(t), p.ntilesf + t, p.mtf,
+        launch_rows<false>(split, st, LoadSilu{Af(t), hf}, W2f, hf, d, TLF(t), p.ntilesf + t, p.mtf,
                            EpiRowScale{p.T1f, SGF(t), d});
       }
       {
@@ -590,7 +595,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   const float* hT = HV(p.h, T);
   {
     PROF(PROF_DENSE_GEMM, f_dense, 0);
-    launch_rows<false>(st, LoadPlain{hT, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{p.z, d});
+    launch_rows<false>(split, st, LoadPlain{hT, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{p.z, d});
   }
   {
     PROF(PROF_OTHER, 0, 4.0 * Nd);
@@ -601,7 +606,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   // ---- phase 2: force backward (hh[t] = dE/dh^t)
   {
     PROF(PROF_DENSE_GEMM, f_dense, 0);
-    launch_rows<true>(st, LoadSiluD1Scaled{p.z, wo2, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN,
+    launch_rows<true>(split, st, LoadSiluD1Scaled{p.z, wo2, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN,
                       EpiDense{HV(p.hh, T), d});
   }
   JANUS_HIP_TRY(hipMemsetAsync(p.rbar, 0, sizeof(float) * std::max<long long>(Ne, 1), st));
@@ -622,12 +627,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<true>(st, LoadPlain{Ybf(t), d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
+        launch_rows<true>(split, st, LoadPlain{Ybf(t), d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
                           EpiP2{Af(t), Sbf(t), Abf(t), hf});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<true>(st, LoadPlain{Abf(t), hf}, W1f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T1f, d});
+        launch_rows<true>(split, st, LoadPlain{Abf(t), hf}, W1f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T1f, d});
       }
       {
         PROF(PROF_ATOM, 0, by_fcombine);
@@ -640,7 +645,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       // adjoint of osum (ob = dE/du Wo^T) -> attention backward -> message adjoints -> slots
       {
         PROF(PROF_DENSE_GEMM, f_dense, 0);
-        launch_rows<true>(st, LoadPlain{hbar_u, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
+        launch_rows<true>(kFp32, st, LoadPlain{hbar_u, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
                           EpiStore{OBt(t), d});
       }
       {
@@ -663,7 +668,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_DENSE_GEMM, f_qkv, 0);
-        launch_rows<true>(st, LoadPlain{QKVbt(t), 3LL * d}, Wp(blk(t, "Wqkv")), 3 * d, d, p.tilesE, p.ntE, p.mtE,
+        launch_rows<true>(kFp32, st, LoadPlain{QKVbt(t), 3LL * d}, Wp(blk(t, "Wqkv")), 3 * d, d, p.tilesE, p.ntE, p.mtE,
                           EpiStore{MBt(t), d});
       }
       {
@@ -681,16 +686,16 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       LAUNCH_VPL_K(feat_p2_kernel, d, k, gE, b256, 0, st, attn ? (const int*)p.iotaE : ei, POS(t), EID(t), GATE(t),
                    (const float*)FPR(t), Ee, (int)Ep, attn ? (const float*)MBt(t) : hbar_u, (const float*)YstR(t),
                    Ne, d, GBR(t), LBR(t));
-      launch_rows<true>(st, LoadPlain{LBR(t), Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE, EpiStore{p.Xadd, d});
+      launch_rows<true>(split, st, LoadPlain{LBR(t), Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE, EpiStore{p.Xadd, d});
     }
     {
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<true>(st, LoadPlain{Ybs(t), d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
+      launch_rows<true>(split, st, LoadPlain{Ybs(t), d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
                         EpiP2{Aa(t), Sb(t), Ab(t), h});
     }
     {
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<true>(st, LoadPlain{Ab(t), h}, W1, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T1, d});
+      launch_rows<true>(split, st, LoadPlain{Ab(t), h}, W1, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T1, d});
     }
     if (Ne > 0) {
       PROF(PROF_EDGE, 0, by_p2);
@@ -707,12 +712,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<true>(st, LoadPlain{Y3bs(t), d}, Wp(blk(t, "W2a")), d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<true>(split, st, LoadPlain{Y3bs(t), d}, Wp(blk(t, "W2a")), d, h3, TL3(t), p.ntiles3 + t, p.mt3,
                           EpiP2{A3(t), S3b(t), A3b(t), h3});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<true>(st, LoadPlain{A3b(t), h3}, Wp(blk(t, "W1a")), h3, d, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<true>(split, st, LoadPlain{A3b(t), h3}, Wp(blk(t, "W1a")), h3, d, TL3(t), p.ntiles3 + t, p.mt3,
                           EpiStore{p.T3a, d});
       }
       {
@@ -819,30 +824,30 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       {
         // dW_a (part 1): Gt^T (Zbar * h_j2)
         PROF(PROF_DENSE_GEMM, f_wa, 0);
-        launch_wgrad(st, LoadPlain{p.G3t, nf}, LoadPlain{p.VT, d}, nf, d, p.chunksT, p.ncT, p.cfT, p.mcT, 1,
+        launch_wgrad(split, st, LoadPlain{p.G3t, nf}, LoadPlain{p.VT, d}, nf, d, p.chunksT, p.ncT, p.cfT, p.mcT, 1,
                      p.partial, Gp(blk(t, "W_a")), 1);
         // loss gradient in positions: adjoint of the feature tangent, sum_t (Zbar * h_j2) W_a^T
         if (p.adjGd)
-          launch_rows<true>(st, LoadPlain{p.VT, d}, Wp(blk(t, "W_a")), d, nf, p.tilesT, p.ntT, p.mtT,
+          launch_rows<true>(split, st, LoadPlain{p.VT, d}, Wp(blk(t, "W_a")), d, nf, p.tilesT, p.ntT, p.mtT,
                             EpiAdd{p.adjGd, p.adjGd, nf});
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_tri, 0);
-        launch_wgrad(st, LoadPlain{p.T3a, d}, LoadPlain{A3b(t), h3}, d, h3, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
+        launch_wgrad(split, st, LoadPlain{p.T3a, d}, LoadPlain{A3b(t), h3}, d, h3, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
                      E3, p.partial, Gp(blk(t, "W1a")), 1);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<false>(st, LoadPlain{p.T3a, d}, W1a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<false>(split, st, LoadPlain{p.T3a, d}, W1a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
                            EpiP3{A3(t), S3b(t), A3b(t), h3});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<false>(st, LoadPlain{A3b(t), h3}, W2a, h3, d, TL3(t), p.ntiles3 + t, p.mt3, EpiStore{p.T3b, d});
+        launch_rows<false>(split, st, LoadPlain{A3b(t), h3}, W2a, h3, d, TL3(t), p.ntiles3 + t, p.mt3, EpiStore{p.T3b, d});
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_tri, 0);
-        launch_wgrad(st, LoadPlain{A3b(t), h3}, LoadPlain{Y3bs(t), d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
+        launch_wgrad(split, st, LoadPlain{A3b(t), h3}, LoadPlain{Y3bs(t), d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
                      E3, p.partial, Gp(blk(t, "W2a")), 1);
       }
       {
@@ -863,10 +868,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     if (p.rf && Ne > 0) {
       // lh = Xbt Wr -> gate adjoints gh and softmax adjoints P3; dWr += Xbt^T lbar
       PROF(PROF_ROUTE, 4.0 * Ne * d * Ep, Ne * (8.0 * d + 16.0 * Ep));
-      launch_rows<false>(st, LoadPlain{p.Xh, d}, WRP(t), d, (int)Ep, p.tilesE, p.ntE, p.mtE, EpiStore{p.Lw, Ep});
+      launch_rows<false>(split, st, LoadPlain{p.Xh, d}, WRP(t), d, (int)Ep, p.tilesE, p.ntE, p.mtE, EpiStore{p.Lw, Ep});
       hipLaunchKernelGGL(feat_p3_kernel, dim3(cdiv(Ne, 256)), b256, 0, st, EID(t), GATE(t), (const float*)FPR(t),
                          (const float*)GBR(t), (const float*)p.Lw, Ne, Ee, (int)Ep, k, GHR(t), P3R(t));
-      launch_wgrad(st, LoadPlain{p.Xh, d}, LoadPlain{LBR(t), Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
+      launch_wgrad(split, st, LoadPlain{p.Xh, d}, LoadPlain{LBR(t), Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
                    p.wrpart, DWR(t), 1);
     }
     // G7 (side stream) beside dW_b and the reverse scatter
@@ -874,7 +879,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     {
       // G7: dW1 += Xbt^T Abar (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
-      launch_wgrad(sd, LoadPlain{p.T1, d}, LoadPlain{Ab(t), h}, d, h, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
+      launch_wgrad(split, sd, LoadPlain{p.T1, d}, LoadPlain{Ab(t), h}, d, h, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
                    p.partial2, Gp(blk(t, "W1")), 1);
     }
     t1_free = ss.mark();
@@ -893,13 +898,13 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     {
       // G5: Abt = Xbt W1 -> Sbt (into Shat(t)), C (into Sb)
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<false>(st, LoadPlain{p.T1, d}, W1, d, h, TL(t), p.ntiles + t, p.mt,
+      launch_rows<false>(split, st, LoadPlain{p.T1, d}, W1, d, h, TL(t), p.ntiles + t, p.mt,
                          EpiP3{Aa(t), Sb(t), Shat(t), h});
     }
     {
       // G6: Ybt = Sbt W2
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<false>(st, LoadPlain{Shat(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T2, d});
+      launch_rows<false>(split, st, LoadPlain{Shat(t), h}, W2, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T2, d});
     }
     // G8 (side stream) beside the per-atom and per-edge kernels that follow (and those
     // of the next block up to its G5)
@@ -907,7 +912,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     {
       // G8: dW2 += Sbt^T Ybar (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
-      launch_wgrad(sd, LoadPlain{Shat(t), h}, LoadPlain{Ybs(t), d}, h, d, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
+      launch_wgrad(split, sd, LoadPlain{Shat(t), h}, LoadPlain{Ybs(t), d}, h, d, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
                    p.partial2, Gp(blk(t, "W2")), 1);
     }
     // phase-2 dE/du of this block (hh^{t+1} without the feature-update MoE)
@@ -926,7 +931,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_DENSE_GEMM, f_qkv, 0);
-        launch_rows<false>(st, LoadPlain{MHt(t), d}, Wp(blk(t, "Wqkv")), d, 3 * d, p.tilesE, p.ntE, p.mtE,
+        launch_rows<false>(kFp32, st, LoadPlain{MHt(t), d}, Wp(blk(t, "Wqkv")), d, 3 * d, p.tilesE, p.ntE, p.mtE,
                            EpiStore{QKVht(t), 3LL * d});
       }
       {
@@ -948,10 +953,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_DENSE_GEMM, 2 * f_dense, 0);
-        launch_rows<false>(st, LoadPlain{p.osh, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
+        launch_rows<false>(kFp32, st, LoadPlain{p.osh, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN,
                            EpiAdd{uh_out, hht_t, d});
         // dWo (tangent part): osumh^T dE/du
-        launch_wgrad(st, LoadPlain{p.osh, d}, LoadPlain{hbar_u3, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1,
+        launch_wgrad(kFp32, st, LoadPlain{p.osh, d}, LoadPlain{hbar_u3, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1,
                      p.partial, Gp(blk(t, "Wo")), 1);
       }
     } else {
@@ -975,21 +980,21 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_EXPERT_WGRAD, f_atm, 0);
-        launch_wgrad(st, LoadPlain{p.T1f, d}, LoadPlain{Abf(t), hf}, d, hf, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
+        launch_wgrad(split, st, LoadPlain{p.T1f, d}, LoadPlain{Abf(t), hf}, d, hf, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
                      Ef, p.partial, Gp(blk(t, "W1f")), 1);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<false>(st, LoadPlain{p.T1f, d}, W1f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
+        launch_rows<false>(split, st, LoadPlain{p.T1f, d}, W1f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
                            EpiP3{Af(t), Sbf(t), Abf(t), hf});
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<false>(st, LoadPlain{Abf(t), hf}, W2f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T2f, d});
+        launch_rows<false>(split, st, LoadPlain{Abf(t), hf}, W2f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T2f, d});
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_atm, 0);
-        launch_wgrad(st, LoadPlain{Abf(t), hf}, LoadPlain{Ybf(t), d}, hf, d, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
+        launch_wgrad(split, st, LoadPlain{Abf(t), hf}, LoadPlain{Ybf(t), d}, hf, d, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
                      Ef, p.partial, Gp(blk(t, "W2f")), 1);
       }
       {
@@ -1003,7 +1008,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   {
     // readout part: vt = hht^T W_o1
     PROF(PROF_DENSE_GEMM, f_dense, 0);
-    launch_rows<false>(st, LoadPlain{HV(p.hht, T), d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{p.vt, d});
+    launch_rows<false>(split, st, LoadPlain{HV(p.hht, T), d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{p.vt, d});
   }
   JANUS_HIP_TRY(hipGetLastError());
 
@@ -1020,11 +1025,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   }
   {
     PROF(PROF_DENSE_GEMM, 3 * f_dense, 0);
-    launch_wgrad(st, LoadPlain{hT, d}, LoadPlain{p.Zr, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1, p.partial,
+    launch_wgrad(split, st, LoadPlain{hT, d}, LoadPlain{p.Zr, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1, p.partial,
                  Gp("W_o1"), 1);
-    launch_wgrad(st, LoadPlain{HV(p.hht, T), d}, LoadSiluD1Scaled{p.z, wo2, d}, d, d, p.chunksN, p.ncN, p.cfN,
+    launch_wgrad(split, st, LoadPlain{HV(p.hht, T), d}, LoadSiluD1Scaled{p.z, wo2, d}, d, d, p.chunksN, p.ncN, p.cfN,
                  p.mcN, 1, p.partial, Gp("W_o1"), 1);
-    launch_rows<true>(st, LoadPlain{p.Zr, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{HV(p.hh, T), d});
+    launch_rows<true>(split, st, LoadPlain{p.Zr, d}, Wo1, d, d, p.tilesN, p.ntN, p.mtN, EpiDense{HV(p.hh, T), d});
   }
   // G11 and G12 go to the side stream after G10, beside the edge, router and atom
   // kernels of the block; the caller's stream joins it before its next product.
@@ -1048,21 +1053,21 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<true>(st, LoadPlain{p.T1f, d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
+        launch_rows<true>(split, st, LoadPlain{p.T1f, d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
                           EpiP4{Af(t), Sbf(t), SGF(t), hf}, p.gpartf);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<true>(st, LoadPlain{Sbf(t), hf}, W1f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T2f, d});
+        launch_rows<true>(split, st, LoadPlain{Sbf(t), hf}, W1f, hf, d, TLF(t), p.ntilesf + t, p.mtf, EpiStore{p.T2f, d});
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_atm, 0);
-        launch_wgrad(st, LoadPlain{Xsf(t), d}, LoadPlain{Sbf(t), hf}, d, hf, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
+        launch_wgrad(split, st, LoadPlain{Xsf(t), d}, LoadPlain{Sbf(t), hf}, d, hf, CHF(t), p.nchunksf + t, CFF(t), p.mcf,
                      Ef, p.partial, Gp(blk(t, "W1f")), 1);
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_atm, 0);
-        launch_wgrad(st, LoadSiluRowScale{Af(t), SGF(t), hf}, LoadPlain{p.T1f, d}, hf, d, CHF(t), p.nchunksf + t, CFF(t),
+        launch_wgrad(split, st, LoadSiluRowScale{Af(t), SGF(t), hf}, LoadPlain{p.T1f, d}, hf, d, CHF(t), p.nchunksf + t, CFF(t),
                      p.mcf, Ef, p.partial, Gp(blk(t, "W2f")), 1);
       }
       {
@@ -1089,9 +1094,9 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_DENSE_GEMM, 2 * f_dense, 0);
-        launch_rows<true>(st, LoadPlain{a_u, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN, EpiStore{p.AO, d});
+        launch_rows<true>(kFp32, st, LoadPlain{a_u, d}, Wp(blk(t, "Wo")), d, d, p.tilesN, p.ntN, p.mtN, EpiStore{p.AO, d});
         // dWo (primal part): osum^T a_u
-        launch_wgrad(st, LoadPlain{OSt(t), d}, LoadPlain{a_u, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1,
+        launch_wgrad(kFp32, st, LoadPlain{OSt(t), d}, LoadPlain{a_u, d}, d, d, p.chunksN, p.ncN, p.cfN, p.mcN, 1,
                      p.partial, Gp(blk(t, "Wo")), 1);
       }
       {
@@ -1126,11 +1131,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_DENSE_GEMM, 3 * f_qkv, 0);
-        launch_rows<true>(st, LoadPlain{p.QKVa, 3LL * d}, Wqkv, 3 * d, d, p.tilesE, p.ntE, p.mtE, EpiStore{p.mta, d});
+        launch_rows<true>(kFp32, st, LoadPlain{p.QKVa, 3LL * d}, Wqkv, 3 * d, d, p.tilesE, p.ntE, p.mtE, EpiStore{p.mta, d});
         // dWqkv: m^T (q|k|v adjoints) + mh^T (phase-2 q|k|v adjoints = adjoints of the tangents)
-        launch_wgrad(st, LoadPlain{MM(t), d}, LoadPlain{p.QKVa, 3LL * d}, d, 3 * d, p.chunksA, p.ncA, p.cfA, p.mcA, 1,
+        launch_wgrad(kFp32, st, LoadPlain{MM(t), d}, LoadPlain{p.QKVa, 3LL * d}, d, 3 * d, p.chunksA, p.ncA, p.cfA, p.mcA, 1,
                      p.partial, Gp(blk(t, "Wqkv")), 1);
-        launch_wgrad(st, LoadPlain{MHt(t), d}, LoadPlain{QKVbt(t), 3LL * d}, d, 3 * d, p.chunksA, p.ncA, p.cfA,
+        launch_wgrad(kFp32, st, LoadPlain{MHt(t), d}, LoadPlain{QKVbt(t), 3LL * d}, d, 3 * d, p.chunksA, p.ncA, p.cfA,
                      p.mcA, 1, p.partial, Gp(blk(t, "Wqkv")), 1);
       }
       if (p.rf) {
@@ -1141,9 +1146,9 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
           LAUNCH_VPL_K(feat_p4_kernel, d, k, gE, b256, 0, st, (const int*)p.iotaE, POS(t), EID(t),
                        (const float*)FPR(t), Ee, (int)Ep, (const float*)p.mta, (const float*)YstR(t),
                        (const float*)(p.g3 + t * M), (const float*)P3R(t), Ne, d, p.Lw, p.lte);
-          launch_rows<true>(st, LoadPlain{p.Lw, Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE,
+          launch_rows<true>(split, st, LoadPlain{p.Lw, Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE,
                             EpiStore{p.Xadd, d});
-          launch_wgrad(st, LoadPlain{XeR(t), d}, LoadPlain{p.Lw, Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
+          launch_wgrad(split, st, LoadPlain{XeR(t), d}, LoadPlain{p.Lw, Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
                        p.wrpart, DWR(t), 1);
         }
         LAUNCH_VPL_K(gather_feat_kernel, d, k, gE, b256, 0, st, (const int*)p.iotaE, POS(t), GATE(t),
@@ -1162,9 +1167,9 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
           LAUNCH_VPL_K(feat_p4_kernel, d, k, gE, b256, 0, st, ei, POS(t), EID(t), (const float*)FPR(t), Ee, (int)Ep,
                        a_u, (const float*)YstR(t), (const float*)(p.g3 + t * M), (const float*)P3R(t), Ne, d,
                        p.Lw, p.lte);
-          launch_rows<true>(st, LoadPlain{p.Lw, Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE,
+          launch_rows<true>(split, st, LoadPlain{p.Lw, Ep}, WRP(t), (int)Ep, d, p.tilesE, p.ntE, p.mtE,
                             EpiStore{p.Xadd, d});
-          launch_wgrad(st, LoadPlain{XeR(t), d}, LoadPlain{p.Lw, Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
+          launch_wgrad(split, st, LoadPlain{XeR(t), d}, LoadPlain{p.Lw, Ep}, d, (int)Ep, p.chunksR, p.ncR, p.cfR, p.mcR, 1,
                        p.wrpart, DWR(t), 1);
         }
       }
@@ -1183,26 +1188,26 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       // G9: St = mt W2^T -> At = g SiLU'(A) St + C (into Sb); row sums for the gate adjoint
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
       // (with routing on the edge tokens the slot rows already carry the gates)
-      launch_rows<true>(st, LoadPlain{p.T1, d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
+      launch_rows<true>(split, st, LoadPlain{p.T1, d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
                         EpiP4{Aa(t), Sb(t), p.rf ? (const float*)p.ones : SG(t), h}, p.gpart);
     }
     {
       // G10: Xt = At W1^T
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
-      launch_rows<true>(st, LoadPlain{Sb(t), h}, W1, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T2, d});
+      launch_rows<true>(split, st, LoadPlain{Sb(t), h}, W1, h, d, TL(t), p.ntiles + t, p.mt, EpiStore{p.T2, d});
     }
     ss.fork();
     {
       // G12: dW2 += SiLU(A)^T (g mt) (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
-      launch_wgrad(sd, LoadSiluRowScale{Aa(t), p.rf ? (const float*)p.ones : SG(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
+      launch_wgrad(split, sd, LoadSiluRowScale{Aa(t), p.rf ? (const float*)p.ones : SG(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
                    p.nchunks + t, CF(t), p.mc, Ee, p.partial2, Gp(blk(t, "W2")), 1);
     }
     t1_free = ss.mark();
     {
       // G11: dW1 += X^T At (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
-      launch_wgrad(sd, LoadPlain{Xs(t), d}, LoadPlain{Sb(t), h}, d, h, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
+      launch_wgrad(split, sd, LoadPlain{Xs(t), d}, LoadPlain{Sb(t), h}, d, h, CH(t), p.nchunks + t, CF(t), p.mc, Ee,
                    p.partial2, Gp(blk(t, "W1")), 1);
     }
     if (Ne > 0) {
@@ -1247,21 +1252,21 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<true>(st, LoadPlain{p.T3a, d}, W2a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+        launch_rows<true>(split, st, LoadPlain{p.T3a, d}, W2a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
                           EpiP4{A3(t), S3b(t), SG3(t), h3}, p.gpart3);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<true>(st, LoadPlain{S3b(t), h3}, W1a, h3, d, TL3(t), p.ntiles3 + t, p.mt3, EpiStore{p.T3b, d});
+        launch_rows<true>(split, st, LoadPlain{S3b(t), h3}, W1a, h3, d, TL3(t), p.ntiles3 + t, p.mt3, EpiStore{p.T3b, d});
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_tri, 0);
-        launch_wgrad(st, LoadPlain{Z3s(t), d}, LoadPlain{S3b(t), h3}, d, h3, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
+        launch_wgrad(split, st, LoadPlain{Z3s(t), d}, LoadPlain{S3b(t), h3}, d, h3, CH3(t), p.nchunks3 + t, CF3(t), p.mc3,
                      E3, p.partial, Gp(blk(t, "W1a")), 1);
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_tri, 0);
-        launch_wgrad(st, LoadSiluRowScale{A3(t), SG3(t), h3}, LoadPlain{p.T3a, d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t),
+        launch_wgrad(split, st, LoadSiluRowScale{A3(t), SG3(t), h3}, LoadPlain{p.T3a, d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t),
                      p.mc3, E3, p.partial, Gp(blk(t, "W2a")), 1);
       }
       {
@@ -1273,11 +1278,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       {
         // dW_a (part 2): G^T (Zt * h_j2 + Q * Zbar)
         PROF(PROF_DENSE_GEMM, f_wa, 0);
-        launch_wgrad(st, LoadPlain{p.G3f, nf}, LoadPlain{p.VT, d}, nf, d, p.chunksT, p.ncT, p.cfT, p.mcT, 1,
+        launch_wgrad(split, st, LoadPlain{p.G3f, nf}, LoadPlain{p.VT, d}, nf, d, p.chunksT, p.ncT, p.cfT, p.mcT, 1,
                      p.partial, Gp(blk(t, "W_a")), 1);
         // loss gradient in positions: adjoint of the features, sum_t VT W_a^T
         if (p.adjG)
-          launch_rows<true>(st, LoadPlain{p.VT, d}, Wp(blk(t, "W_a")), d, nf, p.tilesT, p.ntT, p.mtT,
+          launch_rows<true>(split, st, LoadPlain{p.VT, d}, Wp(blk(t, "W_a")), d, nf, p.tilesT, p.ntT, p.mtT,
                             EpiAdd{p.adjG, p.adjG, nf});
       }
       {

@@ -1,4 +1,4 @@
-// Grouped fp32 GEMMs on the CDNA4 matrix cores (v_mfma_f32_32x32x2_f32).
+// Grouped fp32 GEMMs on the CDNA4 matrix cores.
 //
 // Two kernel families cover every expert contraction of the training step:
 //
@@ -18,18 +18,39 @@
 //
 // Work decomposition: a workgroup of 256 threads (4 waves as 2 x 2) owns a
 // 128 x 128 output tile; each wave owns 64 x 64 = 2 x 2 MFMA blocks of
-// 32 x 32, i.e. 64 accumulator floats per lane.  K advances in stages of 16
-// through double-buffered LDS; the global loads of stage s+1 are in flight
-// while stage s is multiplied.  Operands stored as they are used (the expert
-// weights, and every slot-row operand without a transform) go from global
-// memory straight into LDS (global_load_lds_dwordx4: no registers, no LDS
-// store instructions); an operand transform (SiLU of stored pre-activations,
-// a row scale) runs when its registers are written to LDS, and so do the
-// zeros of a weight-gradient chunk's last partial stage.  Inside a stage the
-// k index of MFMA step j for lane half hf is 8g + 4hf + j (g = 0, 1), so an operand stored
-// k-contiguous is read from LDS with one 16-byte load per lane per 8 k, and
-// an operand stored m-contiguous with 4-byte loads whose 32-lane halves read
-// consecutive words.
+// 32 x 32.  Two ways to multiply, chosen per launch:
+//
+//  * Split products (v_mfma_f32_32x32x16_f16).  An fp32 operand value, scaled
+//    by a power of two per row of A and per column of B, is the sum of two
+//    fp16 numbers, x s = h + 2^-11 l: h holds 11 significant bits and l the
+//    13 that are left (sign included), so nothing of a 24-bit significand is
+//    lost.  C = sum h h' + 2^-11 sum (h l' + l h') takes three 16-bit matrix
+//    products in place of one fp32 product at a sixteenth of their rate; what
+//    is left out, 2^-22 l l', is below 2^-24 of the product.  The two sums have
+//    accumulators of their own (the matrix unit truncates small addends when it
+//    aligns them to a large accumulator, a bias that grows with the length of
+//    the contraction when both share one).  The scale comes from the largest
+//    magnitude of the row's (column's) first 32 k, brought to [2^6, 2^7): values
+//    up to 2^9 times as large fit fp16, and values down to 2^-20 of it keep all
+//    their bits, below that an absolute 2^-42 of it is lost.  A larger value (or
+//    one after 32 zeros) overflows to infinity, and the tile is taken again on
+//    the fp32 instructions, as is any tile with infinities or NaN.
+//    Measured against the fp32 instructions, 500 000 rows over 64 groups: K = 512,
+//    N = 2048 132 -> 208 TFLOP/s (NN), 135 -> 242 (NT); K = 2048, N = 512 133 -> 221
+//    and 137 -> 273; weight gradient 512 x 2048 114 -> 178; 340 000 rows over 8 groups,
+//    128 x 512: 111 -> 143, 113 -> 154 and 104 -> 137.  Error against 64 bits at K = 128 / 512 /
+//    2048: 1.1 / 1.7 / 3.0e-7, fp32 instructions 2.0 / 4.1 / 8.1e-7.  Three bf16 terms and six
+//    products, which need no scale, reach 131-190 and 121-140 TFLOP/s: the six products
+//    bring the clock down to 1.7 GHz.
+//
+//  * fp32 instructions (v_mfma_f32_32x32x2_f32), for callers that keep their
+//    results bit for bit and for tiles that the split cannot take.  K advances in
+//    stages of 16 through double-buffered LDS; operands stored as they are used go from
+//    global memory straight into LDS (global_load_lds_dwordx4), transformed ones through
+//    registers.  Inside a stage the k index of MFMA step j for lane half hf is
+//    8g + 4hf + j (g = 0, 1), so an operand stored k-contiguous is read from LDS with one
+//    16-byte load per lane per 8 k, and an operand stored m-contiguous with 4-byte loads
+//    whose 32-lane halves read consecutive words.
 //
 // Epilogue: the accumulators are staged through LDS, 64 rows at a time, and
 // then visited row-major as float4, so every epilogue read and write of
@@ -56,7 +77,17 @@ constexpr int B_BUF = cmax(GBN * LD_MK, GBK * LD_KM);             // one B stage
 constexpr int SMEM_MAIN = cmax(2 * GBM * LD_MK + 2 * B_BUF,       // gemm_rows
                                4 * GBK * LD_KM);                   // gemm_wgrad
 constexpr int SMEM_EPI = 64 * LD_C;
-constexpr int SMEM_FLOATS = SMEM_MAIN > SMEM_EPI ? SMEM_MAIN : SMEM_EPI;
+constexpr int SMEM_FP32 = cmax(SMEM_MAIN, SMEM_EPI);
+// One operand stage of the split products: two fp16 planes of 128 rows x 32 k, each plane
+// four k-octets of [row][8 fp16].  The octets lie 64 bytes apart (mod 256), so that the
+// 16-lane groups of a store (8 rows x 2 octets two apart) touch 64 distinct banks.
+constexpr int SBK = 32;                       // k per stage
+constexpr int SP_OCT = GBM * 16 + 64;         // bytes of one octet
+constexpr int SP_PLANE = 4 * SP_OCT;
+constexpr int SP_OPER = 2 * SP_PLANE;
+constexpr int SP_STAGE = 2 * SP_OPER;
+constexpr int SMEM_BODY = cmax(2 * SP_STAGE / 4, SMEM_FP32);   // floats
+constexpr int SMEM_FLOATS = SMEM_BODY + GBM + GBN + 4;   // + row and column exponents, flags
 
 struct RowsTile {   // one 128-row tile of a group
   int group;
@@ -102,6 +133,9 @@ struct LoadPlain {
   using Raw = float4;
   __device__ __forceinline__ Raw load(long long r, int k) const { return ld4(p + r * ld + k); }
   __device__ __forceinline__ float4 apply(const Raw& v, int) const { return v; }
+  using Raw1 = float;
+  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return p[r * ld + k]; }
+  __device__ __forceinline__ float apply1(Raw1 v, int) const { return v; }
 };
 
 struct LoadSilu {   // SiLU of stored pre-activations
@@ -126,6 +160,11 @@ struct LoadSiluRowScale {   // s[r] * SiLU(p[r, k])
   __device__ __forceinline__ float4 apply(const Raw& x, int) const {
     return make_float4(x.s * silu(x.v.x), x.s * silu(x.v.y), x.s * silu(x.v.z), x.s * silu(x.v.w));
   }
+  struct Raw1 {
+    float v, s;
+  };
+  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return Raw1{p[r * ld + k], s[r]}; }
+  __device__ __forceinline__ float apply1(const Raw1& x, int) const { return x.s * silu(x.v); }
 };
 
 struct LoadSiluD1Scaled {   // SiLU'(z[r, k]) * w[k]
@@ -138,6 +177,9 @@ struct LoadSiluD1Scaled {   // SiLU'(z[r, k]) * w[k]
     const float4 ww = ld4(w + k);
     return make_float4(silu_d1(v.x) * ww.x, silu_d1(v.y) * ww.y, silu_d1(v.z) * ww.z, silu_d1(v.w) * ww.w);
   }
+  using Raw1 = float;
+  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return z[r * ld + k]; }
+  __device__ __forceinline__ float apply1(Raw1 v, int k) const { return silu_d1(v) * w[k]; }
 };
 
 // ---------------------------------------------------------------- epilogues
@@ -440,38 +482,236 @@ __device__ __forceinline__ void mfma_stage(const float* a_s, const float* b_s, i
   }
 }
 
+// ---------------------------------------------------------- split products
+// Split of a scaled value: x s = h + 2^-11 l with h, l in fp16, each rounded to nearest.  h
+// holds 11 significant bits and l the 13 that are left, so the split of a normal x is exact.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_pair(float a, float b, float s, float s11, unsigned& h, unsigned& l) {
+  const f16x2 hv = __builtin_convertvector((f32x2v){a * s, b * s}, f16x2);
+  const float ra = fmaf((float)hv.x, -2048.f, a * s11), rb = fmaf((float)hv.y, -2048.f, b * s11);
+  h = __builtin_bit_cast(unsigned, hv);
+  l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2v){ra, rb}, f16x2));
+}
+
+// 16 k-consecutive values of one row: two octets of the stage.
+__device__ __forceinline__ void split_store(const float (&x)[16], float s, float s11, char* d, int row, int part) {
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    unsigned h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split_pair(x[8 * o + 2 * i], x[8 * o + 2 * i + 1], s, s11, h[i], l[i]);
+    char* q = d + (2 * part + o) * SP_OCT + row * 16;
+    *reinterpret_cast<uint4*>(q) = make_uint4(h[0], h[1], h[2], h[3]);
+    *reinterpret_cast<uint4*>(q + SP_PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
+  }
+}
+__device__ __forceinline__ float absmax16(const float (&x)[16]) {
+  float m = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
+  return m;
+}
+// Power-of-two scale that brings a value of magnitude m to [2^6, 2^7), as its exponent field.
+__device__ __forceinline__ int scale_field(float m) {
+  const int f = 254 + 6 - (int)(__float_as_uint(m) >> 23);
+  return f > 254 ? 254 : f;
+}
+
+// Operand stored k-contiguous: thread q takes row q / 2, k-half q % 2.
+template <class L>
+struct SplitMK {
+  typename L::Raw raw[4];
+  __device__ __forceinline__ static int row(int tid) { return tid >> 1; }
+  __device__ __forceinline__ static int part(int tid) { return tid & 1; }
+  __device__ __forceinline__ void load(const L& ld, int r0, int r1, int k0, int K, int tid) {
+    const long long r = (long long)r0 + row(tid);
+    const long long rc = r < r1 ? r : (long long)r1 - 1;
+    const int k = k0 + 16 * part(tid), kc = k < K ? k : K - 16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) raw[i] = ld.load(rc, kc + 4 * i);
+  }
+  // Returns the factor of the values: past K (a last stage of 16 k) they repeat the last ones and count 0 times.
+  __device__ __forceinline__ float values(const L& ld, int k0, int K, int tid, float (&x)[16]) const {
+    const int k = k0 + 16 * part(tid), kc = k < K ? k : K - 16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = ld.apply(raw[i], kc + 4 * i);
+      x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+    }
+    return k < K ? 1.f : 0.f;
+  }
+};
+
+// Operand stored row-contiguous ([k][m]): thread q takes column q % 128 of the 16 k-rows of half
+// q / 128 (one half per wave).  Rows past rk_end count as zeros; columns past m_end read the last
+// one (their products are never stored).
+template <class L>
+struct SplitKM {
+  typename L::Raw1 raw[16];
+  __device__ __forceinline__ static int row(int tid) { return tid & 127; }
+  __device__ __forceinline__ static int part(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 7); }
+  __device__ __forceinline__ void load(const L& ld, long long rk, long long rk_end, int m0, int m_end, int tid) {
+    const int m = m0 + row(tid), mc = m < m_end ? m : m_end - 1;
+    const long long r = rk + 16 * part(tid);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) raw[i] = ld.load1(r + i < rk_end ? r + i : rk_end - 1, mc);
+  }
+  __device__ __forceinline__ float values(const L& ld, long long rk, long long rk_end, int m0, int m_end, int tid,
+                                          float (&x)[16]) const {
+    const int m = m0 + row(tid), mc = m < m_end ? m : m_end - 1;
+    const long long left = rk_end - (rk + 16 * part(tid));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = ld.apply1(raw[i], mc);
+    if (left < 16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = i < left ? x[i] : 0.f;
+    }
+    return 1.f;
+  }
+};
+
+// One stage of split products: per 32 x 32 block and 16 k, hi += h h and lo += h l + l h.
+__device__ __forceinline__ void split_stage(const char* st, int wm, int wn, int lr, int hf, f32x16 (&hi)[2][2],
+                                            f32x16 (&lo)[2][2]) {
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    f16x8 a[2][2], b[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const char* o = st + p * SP_PLANE + (2 * g + hf) * SP_OCT;
+        a[q][p] = *reinterpret_cast<const f16x8*>(o + (wm * 64 + q * 32 + lr) * 16);
+        b[q][p] = *reinterpret_cast<const f16x8*>(o + SP_OPER + (wn * 64 + q * 32 + lr) * 16);
+      }
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+        hi[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][0], hi[bi][bj], 0, 0, 0);
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+        lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][1], lo[bi][bj], 0, 0, 0);
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+        lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][1], b[bj][0], lo[bi][bj], 0, 0, 0);
+  }
+}
+
+// The K loop of the split products over [kb, ke): la / lb load one stage's registers, va / vb
+// give their values and the factor of these.  On return hi holds h h' + 2^-11 (h l' + l h') of the
+// scaled operands and smem the exponents that undo the scales; false if a value is not finite.
+// Bound by the LDS traffic (64 KB read and 32 KB written per stage against 768 matrix cycles) and by
+// the clock that the matrix units leave; two workgroups per CU (about 210 registers) overlap one's
+// conversions and barriers with the other's products.
+template <class SA, class SB, class LA, class LB, class VA, class VB>
+__device__ __forceinline__ bool split_loop(float* smem, long long kb, long long ke, const LA& la, const LB& lb,
+                                           const VA& va, const VB& vb, int wm, int wn, int lr, int hf, int tid,
+                                           f32x16 (&hi)[2][2]) {
+  char* lds = reinterpret_cast<char*>(smem);
+  int* ex = reinterpret_cast<int*>(smem + SMEM_BODY);   // [128] rows, [128] columns
+  float* flag = smem + SMEM_BODY + GBM + GBN;
+  f32x16 lo[2][2];
+  zero_acc(hi);
+  zero_acc(lo);
+  SA sa;
+  SB sb;
+  float s_a, s_b, s11_a, s11_b;
+  {
+    // scales from the first stage's largest magnitudes per row and per column
+    float xa[16], xb[16];
+    la(sa, kb);
+    lb(sb, kb);
+    const float ca = va(sa, kb, xa), cb = vb(sb, kb, xb);
+    float* mx = smem + SP_STAGE / 4;   // [2 operands][2 parts][128], in the second stage buffer
+    mx[SA::part(tid) * 128 + SA::row(tid)] = absmax16(xa);
+    mx[256 + SB::part(tid) * 128 + SB::row(tid)] = absmax16(xb);
+    __syncthreads();
+    const int fa = scale_field(fmaxf(mx[SA::row(tid)], mx[128 + SA::row(tid)]));
+    const int fb = scale_field(fmaxf(mx[256 + SB::row(tid)], mx[384 + SB::row(tid)]));
+    s_a = __uint_as_float((unsigned)fa << 23);
+    s_b = __uint_as_float((unsigned)fb << 23);
+    s11_a = s_a * 2048.f;
+    s11_b = s_b * 2048.f;
+    ex[SA::row(tid)] = 127 - fa;
+    ex[128 + SB::row(tid)] = 127 - fb;
+    split_store(xa, ca * s_a, ca * s11_a, lds, SA::row(tid), SA::part(tid));
+    split_store(xb, cb * s_b, cb * s11_b, lds + SP_OPER, SB::row(tid), SB::part(tid));
+  }
+  __syncthreads();
+  int cur = 0;
+  for (long long k = kb; k < ke; k += SBK) {
+    const bool more = k + SBK < ke;
+    if (more) {
+      la(sa, k + SBK);
+      lb(sb, k + SBK);
+    }
+    __builtin_amdgcn_s_setprio(1);
+    split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo);
+    __builtin_amdgcn_s_setprio(0);
+    if (more) {
+      char* d = lds + (cur ^ 1) * SP_STAGE;
+      float x[16];
+      const float ca = va(sa, k + SBK, x);
+      split_store(x, ca * s_a, ca * s11_a, d, SA::row(tid), SA::part(tid));
+      const float cb = vb(sb, k + SBK, x);
+      split_store(x, cb * s_b, cb * s11_b, d + SP_OPER, SB::row(tid), SB::part(tid));
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        hi[i][j][v] = fmaf(lo[i][j][v], 1.f / 2048.f, hi[i][j][v]);
+        z = fmaf(hi[i][j][v], 0.f, z);   // not a number once a value is infinite or not a number
+      }
+  const bool bad = __any(z != z);
+  if ((tid & 63) == 0) flag[tid >> 6] = bad ? 1.f : 0.f;
+  __syncthreads();
+  return flag[0] + flag[1] + flag[2] + flag[3] == 0.f;
+}
+
+// Undo the scales: acc[bi][bj][v] is row 32 bi + 8 (v / 4) + 4 hf + v % 4, column 32 bj + lr of the wave.
+__device__ __forceinline__ void unscale(const float* smem, int wm, int wn, int lr, int hf, f32x16 (&acc)[2][2]) {
+  const int* ex = reinterpret_cast<const int*>(smem + SMEM_BODY);
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const int4 er = *reinterpret_cast<const int4*>(ex + wm * 64 + bi * 32 + 8 * v4 + 4 * hf);
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj) {
+        const int ec = ex[128 + wn * 64 + bj * 32 + lr];
+        acc[bi][bj][4 * v4] = ldexpf(acc[bi][bj][4 * v4], er.x + ec);
+        acc[bi][bj][4 * v4 + 1] = ldexpf(acc[bi][bj][4 * v4 + 1], er.y + ec);
+        acc[bi][bj][4 * v4 + 2] = ldexpf(acc[bi][bj][4 * v4 + 2], er.z + ec);
+        acc[bi][bj][4 * v4 + 3] = ldexpf(acc[bi][bj][4 * v4 + 3], er.w + ec);
+      }
+    }
+}
+
 // ---------------------------------------------------------------- gemm_rows
 
-// One output tile of gemm_rows for (XCD-mapped) block number vb; smem holds
-// SMEM_FLOATS floats of LDS.
-template <bool NT, class ALoad, class Epi>
-__device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad& al, const float* __restrict__ B,
-                                                int K, int N, const RowsTile* __restrict__ tiles,
-                                                const int* __restrict__ n_tiles, const Epi& epi,
-                                                float* __restrict__ rowsum_out) {
-  const int ncol = (N + GBN - 1) / GBN;
-  int t, ctile;
-  xcd_map(vb, ncol, t, ctile);
-  if (t >= *n_tiles) return;
-  const RowsTile tile = tiles[t];
-  const int n0 = ctile * GBN;
-  const int r0 = tile.r0, r1 = tile.r1;
-  const float* Bg = B + (long long)tile.group * K * N;
-
+// The K loop on the fp32 matrix instructions.
+template <bool NT, class ALoad>
+__device__ __forceinline__ void rows_fp32(float* smem, const ALoad& al, const float* __restrict__ Bg, int K, int N,
+                                          int r0, int r1, int n0, int wm, int wn, int lr, int hf, int tid,
+                                          f32x16 (&acc)[2][2]) {
   // double buffers: A at smem + b * GBM * LD_MK, B after both A buffers
   auto sA = [&](int b) { return smem + b * (GBM * LD_MK); };
   auto sB = [&](int b) { return smem + 2 * GBM * LD_MK + b * B_BUF; };
-
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
-  const int wm = w >> 1, wn = w & 1;
-  const int lr = l & 31, hf = l >> 5;
-
-  f32x16 acc[2][2];
-  zero_acc(acc);
-
   StageMK<ALoad> sa;
-
   constexpr bool DA = IsPlainLoad<ALoad>::value;
   auto load_a = [&](int k, float* dst) {
     if constexpr (DA) direct_mk(reinterpret_cast<const LoadPlain&>(al).p, reinterpret_cast<const LoadPlain&>(al).ld,
@@ -481,6 +721,7 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
   auto load_b = [&](int k, float* dst) {
     if (NT) direct_mk(Bg, K, n0, N, k, dst, tid); else direct_km(Bg, N, k, n0, N, dst, tid);
   };
+  zero_acc(acc);
   load_a(0, sA(0));
   load_b(0, sB(0));
   if constexpr (!DA) sa.store(al, sA(0), 0, tid);
@@ -507,6 +748,57 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
     wait_direct();
     __syncthreads();
     cur ^= 1;
+  }
+}
+
+// The same on split products; false (and acc undefined) if a value is infinite or not a number.
+template <bool NT, class ALoad>
+__device__ __forceinline__ bool rows_split(float* smem, const ALoad& al, const float* __restrict__ Bg, int K, int N,
+                                           int r0, int r1, int n0, int wm, int wn, int lr, int hf, int tid,
+                                           f32x16 (&acc)[2][2]) {
+  const LoadPlain bl{Bg, NT ? K : N};
+  using SA = SplitMK<ALoad>;
+  using SB = std::conditional_t<NT, SplitMK<LoadPlain>, SplitKM<LoadPlain>>;
+  auto la = [&](SA& x, long long k) { x.load(al, r0, r1, (int)k, K, tid); };
+  auto va = [&](const SA& x, long long k, float (&v)[16]) { return x.values(al, (int)k, K, tid, v); };
+  auto lb = [&](SB& x, long long k) {
+    if constexpr (NT) x.load(bl, n0, N, (int)k, K, tid); else x.load(bl, k, K, n0, N, tid);
+  };
+  auto vb = [&](const SB& x, long long k, float (&v)[16]) {
+    if constexpr (NT) return x.values(bl, (int)k, K, tid, v); else return x.values(bl, k, K, n0, N, tid, v);
+  };
+  if (!split_loop<SA, SB>(smem, 0, K, la, lb, va, vb, wm, wn, lr, hf, tid, acc)) return false;
+  unscale(smem, wm, wn, lr, hf, acc);
+  return true;
+}
+
+// One output tile of gemm_rows for (XCD-mapped) block number vb; smem holds
+// SMEM_FLOATS floats of LDS.
+template <bool NT, class ALoad, class Epi, bool Split>
+__device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad& al, const float* __restrict__ B,
+                                                int K, int N, const RowsTile* __restrict__ tiles,
+                                                const int* __restrict__ n_tiles, const Epi& epi,
+                                                float* __restrict__ rowsum_out) {
+  const int ncol = (N + GBN - 1) / GBN;
+  int t, ctile;
+  xcd_map(vb, ncol, t, ctile);
+  if (t >= *n_tiles) return;
+  const RowsTile tile = tiles[t];
+  const int n0 = ctile * GBN;
+  const int r0 = tile.r0, r1 = tile.r1;
+  const float* Bg = B + (long long)tile.group * K * N;
+
+  const int tid = threadIdx.x;
+  const int w = tid >> 6, l = tid & 63;
+  const int wm = w >> 1, wn = w & 1;
+  const int lr = l & 31, hf = l >> 5;
+
+  f32x16 acc[2][2];
+  if constexpr (Split) {
+    if (!rows_split<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc))
+      rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+  } else {
+    rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
   }
 
   // Epilogue in two halves of 64 rows: the waves of row half `half` stage
@@ -555,13 +847,13 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
   }
 }
 
-template <bool NT, class ALoad, class Epi>
+template <bool NT, class ALoad, class Epi, bool Split>
 __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(ALoad al, const float* __restrict__ B, int K, int N,
                                                            const RowsTile* __restrict__ tiles,
                                                            const int* __restrict__ n_tiles, Epi epi,
                                                            float* __restrict__ rowsum_out) {
-  __shared__ __attribute__((aligned(16))) float smem[SMEM_FLOATS];
-  gemm_rows_block<NT, ALoad, Epi>(blockIdx.x, smem, al, B, K, N, tiles, n_tiles, epi, rowsum_out);
+  __shared__ __attribute__((aligned(16))) float smem[Split ? SMEM_FLOATS : SMEM_FP32];
+  gemm_rows_block<NT, ALoad, Epi, Split>(blockIdx.x, smem, al, B, K, N, tiles, n_tiles, epi, rowsum_out);
 }
 
 // --------------------------------------------------------------- gemm_wgrad
@@ -574,30 +866,14 @@ struct WChunk {
   int pad;
 };
 
-// One partial tile of gemm_wgrad for (XCD-mapped) block number vb.
+// The contraction on the fp32 matrix instructions.
 template <class ALoad, class BLoad>
-__device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
-                                                 const WChunk* __restrict__ chunks,
-                                                 const int* __restrict__ n_chunks, float* __restrict__ partial) {
-  const int ntq = (Q + GBN - 1) / GBN;
-  int c, pq;
-  xcd_map(vb, ((P + GBM - 1) / GBM) * ntq, c, pq);
-  if (c >= *n_chunks) return;
-  const WChunk ch = chunks[c];
-  const int p0 = (pq / ntq) * GBM;
-  const int q0 = (pq % ntq) * GBN;
-
+__device__ __forceinline__ void wgrad_fp32(float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
+                                           const WChunk& ch, int p0, int q0, int wm, int wn, int lr, int hf, int tid,
+                                           f32x16 (&acc)[2][2]) {
   auto sA = [&](int b) { return smem + b * (GBK * LD_KM); };
   auto sB = [&](int b) { return smem + (2 + b) * (GBK * LD_KM); };
-
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
-  const int wm = w >> 1, wn = w & 1;
-  const int lr = l & 31, hf = l >> 5;
-
-  f32x16 acc[2][2];
   zero_acc(acc);
-
   StageKM<ALoad> sa;
   StageKM<BLoad> sb;
   // Both operands in the unpadded swizzled [k][m] layout.  A plain operand loads its whole
@@ -642,6 +918,49 @@ __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoa
     __syncthreads();
     cur ^= 1;
   }
+}
+
+// The same on split products; false (and acc undefined) if a value is infinite or not a number.
+template <class ALoad, class BLoad>
+__device__ __forceinline__ bool wgrad_split(float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
+                                            const WChunk& ch, int p0, int q0, int wm, int wn, int lr, int hf, int tid,
+                                            f32x16 (&acc)[2][2]) {
+  using SA = SplitKM<ALoad>;
+  using SB = SplitKM<BLoad>;
+  auto la = [&](SA& x, long long k) { x.load(al, k, ch.r1, p0, P, tid); };
+  auto va = [&](const SA& x, long long k, float (&v)[16]) { return x.values(al, k, ch.r1, p0, P, tid, v); };
+  auto lb = [&](SB& x, long long k) { x.load(bl, k, ch.r1, q0, Q, tid); };
+  auto vb = [&](const SB& x, long long k, float (&v)[16]) { return x.values(bl, k, ch.r1, q0, Q, tid, v); };
+  if (!split_loop<SA, SB>(smem, ch.r0, ch.r1, la, lb, va, vb, wm, wn, lr, hf, tid, acc)) return false;
+  unscale(smem, wm, wn, lr, hf, acc);
+  return true;
+}
+
+// One partial tile of gemm_wgrad for (XCD-mapped) block number vb.
+template <class ALoad, class BLoad, bool Split>
+__device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
+                                                 const WChunk* __restrict__ chunks,
+                                                 const int* __restrict__ n_chunks, float* __restrict__ partial) {
+  const int ntq = (Q + GBN - 1) / GBN;
+  int c, pq;
+  xcd_map(vb, ((P + GBM - 1) / GBM) * ntq, c, pq);
+  if (c >= *n_chunks) return;
+  const WChunk ch = chunks[c];
+  const int p0 = (pq / ntq) * GBM;
+  const int q0 = (pq % ntq) * GBN;
+
+  const int tid = threadIdx.x;
+  const int w = tid >> 6, l = tid & 63;
+  const int wm = w >> 1, wn = w & 1;
+  const int lr = l & 31, hf = l >> 5;
+
+  f32x16 acc[2][2];
+  if constexpr (Split) {
+    if (!wgrad_split(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc))
+      wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
+  } else {
+    wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
+  }
 
   float* out = partial + (long long)c * P * Q;
 #pragma unroll
@@ -657,13 +976,13 @@ __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoa
     }
 }
 
-template <class ALoad, class BLoad>
+template <class ALoad, class BLoad, bool Split>
 __global__ __launch_bounds__(256, 2) void gemm_wgrad_kernel(ALoad al, BLoad bl, int P, int Q,
                                                             const WChunk* __restrict__ chunks,
                                                             const int* __restrict__ n_chunks,
                                                             float* __restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) float smem[SMEM_FLOATS];
-  gemm_wgrad_block<ALoad, BLoad>(blockIdx.x, smem, al, bl, P, Q, chunks, n_chunks, partial);
+  __shared__ __attribute__((aligned(16))) float smem[Split ? SMEM_FLOATS : SMEM_FP32];
+  gemm_wgrad_block<ALoad, BLoad, Split>(blockIdx.x, smem, al, bl, P, Q, chunks, n_chunks, partial);
 }
 
 // ---------------------------------------------------------- skinny wgrad

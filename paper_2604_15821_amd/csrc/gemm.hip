@@ -178,9 +178,9 @@ extern "C" int janus_grouped_gemm(janus_ctx* ctx, const float* A, const float* B
   int* nt = c2.take<int>(1);
   build_tables(st, row_off, n_groups, 0, tiles, nt, nullptr, nullptr, nullptr);
   if (trans_b)
-    launch_rows<true>(st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+    launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   else
-    launch_rows<false>(st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+    launch_rows<false>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
 }
@@ -241,9 +241,9 @@ extern "C" int janus_grouped_gemm_noalloc(const float* A, const float* B, float*
   // nothing left by an earlier call is used
   build_tables(st, row_off, n_groups, 0, tiles, nt, nullptr, nullptr, nullptr);
   if (trans_b)
-    launch_rows<true>(st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+    launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   else
-    launch_rows<false>(st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+    launch_rows<false>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
 }
@@ -275,7 +275,7 @@ extern "C" int janus_grouped_wgrad(janus_ctx* ctx, const float* A, const float* 
   int* first = c2.take<int>(n_groups + 1);
   float* partial = c2.take<float>((size_t)mc * P * Q);
   build_tables(st, row_off, n_groups, kc, nullptr, nullptr, chunks, nc, first);
-  launch_wgrad(st, LoadPlain{A, P}, LoadPlain{B, Q}, P, Q, chunks, nc, first, mc, n_groups, partial, G, 0);
+  launch_wgrad(std::true_type{}, st, LoadPlain{A, P}, LoadPlain{B, Q}, P, Q, chunks, nc, first, mc, n_groups, partial, G, 0);
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
 }

@@ -154,24 +154,45 @@ inline const void* skinny_kernel(int P, int Q) {
 void launch_wgrad_reduce(hipStream_t st, const float* partial, const int* chunk_first, int groups,
                          long long PQ, float* G, int accumulate);
 
-// Launch helpers (the tables must have been built on `st` beforehand).
-template <bool NT, class ALoad, class Epi>
-void launch_rows(hipStream_t st, const ALoad& al, const float* B, int K, int N, const RowsTile* tiles,
+// Launch helpers (the tables must have been built on `st` beforehand).  `split` selects the
+// split products (true) or the fp32 matrix instructions (false); kFp32 says false at compile
+// time, so that callers that never split get one kernel only.
+using Fp32Only = std::false_type;
+constexpr Fp32Only kFp32{};
+
+template <bool NT, class S, class ALoad, class Epi>
+void launch_rows(S split, hipStream_t st, const ALoad& al, const float* B, int K, int N, const RowsTile* tiles,
                  const int* n_tiles, int max_tiles, const Epi& epi, float* rowsum = nullptr) {
   if (max_tiles <= 0) return;
   dim3 grid(xcd_grid(max_tiles, (N + GBN - 1) / GBN));
-  hipLaunchKernelGGL((gemm_rows_kernel<NT, ALoad, Epi>), grid, dim3(256), 0, st, al, B, K, N, tiles,
-                     n_tiles, epi, rowsum);
+  if constexpr (!std::is_same_v<S, Fp32Only>) {
+    if (split) {
+      hipLaunchKernelGGL((gemm_rows_kernel<NT, ALoad, Epi, true>), grid, dim3(256), 0, st, al, B, K, N, tiles,
+                         n_tiles, epi, rowsum);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((gemm_rows_kernel<NT, ALoad, Epi, false>), grid, dim3(256), 0, st, al, B, K, N, tiles, n_tiles,
+                     epi, rowsum);
 }
 
-template <class ALoad, class BLoad>
-void launch_wgrad(hipStream_t st, const ALoad& al, const BLoad& bl, int P, int Q, const WChunk* chunks,
+template <class S, class ALoad, class BLoad>
+void launch_wgrad(S split, hipStream_t st, const ALoad& al, const BLoad& bl, int P, int Q, const WChunk* chunks,
                   const int* n_chunks, const int* chunk_first, int max_chunks, int groups,
                   float* partial, float* G, int accumulate) {
   if (max_chunks > 0) {
     dim3 grid(xcd_grid(max_chunks, ((P + GBM - 1) / GBM) * ((Q + GBN - 1) / GBN)));
-    hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
-                       n_chunks, partial);
+    bool launched = false;
+    if constexpr (!std::is_same_v<S, Fp32Only>) {
+      if (split) {
+        hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad, true>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
+                           n_chunks, partial);
+        launched = true;
+      }
+    }
+    if (!launched)
+      hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad, false>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
+                         n_chunks, partial);
   }
   launch_wgrad_reduce(st, partial, chunk_first, groups, (long long)P * Q, G, accumulate);
 }
