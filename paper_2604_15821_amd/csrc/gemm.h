@@ -35,12 +35,17 @@
 //    their bits, below that an absolute 2^-42 of it is lost.  A larger value (or
 //    one after 32 zeros) overflows to infinity, and the tile is taken again on
 //    the fp32 instructions, as is any tile with infinities or NaN.
+//    Two workgroups per CU (about 230 registers); a stage's registers are loaded a whole
+//    stage before they are converted, and the conversion runs in eight parts between the matrix
+//    instructions, so that vector and matrix units work at once.  Left for the end of a stage, on
+//    loads issued at its beginning, the conversion made the stage a serial chain: K = 512, N = 2048
+//    208 TFLOP/s (NN) and 242 (NT), weight gradient 178, against 266, 281 and 248 now.
 //    Measured against the fp32 instructions, 500 000 rows over 64 groups: K = 512,
-//    N = 2048 132 -> 208 TFLOP/s (NN), 135 -> 242 (NT); K = 2048, N = 512 133 -> 221
-//    and 137 -> 273; weight gradient 512 x 2048 114 -> 178; 340 000 rows over 8 groups,
-//    128 x 512: 111 -> 143, 113 -> 154 and 104 -> 137.  Error against 64 bits at K = 128 / 512 /
-//    2048: 1.1 / 1.7 / 3.0e-7, fp32 instructions 2.0 / 4.1 / 8.1e-7.  Three bf16 terms and six
-//    products, which need no scale, reach 131-190 and 121-140 TFLOP/s: the six products
+//    N = 2048 132 -> 266 TFLOP/s (NN), 135 -> 281 (NT); K = 2048, N = 512 133 -> 305
+//    and 137 -> 321; weight gradient 512 x 2048 114 -> 248; 340 000 rows over 8 groups,
+//    128 x 512: 111 -> 163, 113 -> 168 and 104 -> 162 (0.87 GB in 266-275 us).  Error against 64 bits at K = 128 / 512 / 2048: 1.1 / 1.7 / 3.0e-7,
+//    fp32 instructions 2.0 / 4.1 / 8.1e-7.  Three bf16 terms and six products, which need no
+//    scale, reach 131-190 and 121-140 TFLOP/s (with the unspread conversion): the six products
 //    bring the clock down to 1.7 GHz.
 //
 //  * fp32 instructions (v_mfma_f32_32x32x2_f32), for callers that keep their
@@ -79,9 +84,9 @@ constexpr int SMEM_MAIN = cmax(2 * GBM * LD_MK + 2 * B_BUF,       // gemm_rows
 constexpr int SMEM_EPI = 64 * LD_C;
 constexpr int SMEM_FP32 = cmax(SMEM_MAIN, SMEM_EPI);
 // One operand stage of the split products: two fp16 planes of 128 rows x 32 k, each plane
-// four k-octets of [row][8 fp16].  The octets lie 64 bytes apart (mod 256), so that the
-// 16-lane groups of a store (8 rows x 2 octets two apart) touch 64 distinct banks.
-constexpr int SBK = 32;                       // k per stage
+// four k-octets of [row][8 fp16].  The octets lie 64 bytes apart (mod 256), so that the 8-byte
+// stores of 32 lanes (4 rows x 8 k-quads) touch 64 distinct banks.
+constexpr int SBK = 32;                       // k per stage (row products: K is a multiple)
 constexpr int SP_OCT = GBM * 16 + 64;         // bytes of one octet
 constexpr int SP_PLANE = 4 * SP_OCT;
 constexpr int SP_OPER = 2 * SP_PLANE;
@@ -98,6 +103,7 @@ struct RowsTile {   // one 128-row tile of a group
 
 __device__ __forceinline__ float4 f4zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float2 ld2(const float* p) { return *reinterpret_cast<const float2*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 // Streaming accesses of the epilogues (each element is read or written once per launch).
@@ -133,15 +139,16 @@ struct LoadPlain {
   using Raw = float4;
   __device__ __forceinline__ Raw load(long long r, int k) const { return ld4(p + r * ld + k); }
   __device__ __forceinline__ float4 apply(const Raw& v, int) const { return v; }
-  using Raw1 = float;
-  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return p[r * ld + k]; }
-  __device__ __forceinline__ float apply1(Raw1 v, int) const { return v; }
+  static constexpr bool kRowFactor = false;
+  __device__ __forceinline__ const float* base() const { return p; }
+  __device__ __forceinline__ float2 apply2(float2 v, float, int) const { return v; }
 };
 
 struct LoadSilu {   // SiLU of stored pre-activations
   const float* p;
   long long ld;
   using Raw = float4;
+  __device__ __forceinline__ const float* base() const { return p; }
   __device__ __forceinline__ Raw load(long long r, int k) const { return ld4(p + r * ld + k); }
   __device__ __forceinline__ float4 apply(const Raw& v, int) const {
     return make_float4(silu(v.x), silu(v.y), silu(v.z), silu(v.w));
@@ -160,11 +167,11 @@ struct LoadSiluRowScale {   // s[r] * SiLU(p[r, k])
   __device__ __forceinline__ float4 apply(const Raw& x, int) const {
     return make_float4(x.s * silu(x.v.x), x.s * silu(x.v.y), x.s * silu(x.v.z), x.s * silu(x.v.w));
   }
-  struct Raw1 {
-    float v, s;
-  };
-  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return Raw1{p[r * ld + k], s[r]}; }
-  __device__ __forceinline__ float apply1(const Raw1& x, int) const { return x.s * silu(x.v); }
+  static constexpr bool kRowFactor = true;   // apply2's second argument: s[r]
+  __device__ __forceinline__ const float* base() const { return p; }
+  __device__ __forceinline__ float2 apply2(float2 v, float f, int) const {
+    return make_float2(f * silu(v.x), f * silu(v.y));
+  }
 };
 
 struct LoadSiluD1Scaled {   // SiLU'(z[r, k]) * w[k]
@@ -177,9 +184,11 @@ struct LoadSiluD1Scaled {   // SiLU'(z[r, k]) * w[k]
     const float4 ww = ld4(w + k);
     return make_float4(silu_d1(v.x) * ww.x, silu_d1(v.y) * ww.y, silu_d1(v.z) * ww.z, silu_d1(v.w) * ww.w);
   }
-  using Raw1 = float;
-  __device__ __forceinline__ Raw1 load1(long long r, int k) const { return z[r * ld + k]; }
-  __device__ __forceinline__ float apply1(Raw1 v, int k) const { return silu_d1(v) * w[k]; }
+  static constexpr bool kRowFactor = false;
+  __device__ __forceinline__ const float* base() const { return z; }
+  __device__ __forceinline__ float2 apply2(float2 v, float, int k) const {
+    return make_float2(silu_d1(v.x) * w[k], silu_d1(v.y) * w[k + 1]);
+  }
 };
 
 // ---------------------------------------------------------------- epilogues
@@ -488,30 +497,13 @@ __device__ __forceinline__ void mfma_stage(const float* a_s, const float* b_s, i
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split_pair(float a, float b, float s, float s11, unsigned& h, unsigned& l) {
-  const f16x2 hv = __builtin_convertvector((f32x2v){a * s, b * s}, f16x2);
-  const float ra = fmaf((float)hv.x, -2048.f, a * s11), rb = fmaf((float)hv.y, -2048.f, b * s11);
+__device__ __forceinline__ void split_pair(float a, float b, float s, unsigned& h, unsigned& l) {
+  a *= s;
+  b *= s;
+  const f16x2 hv = __builtin_convertvector((f32x2v){a, b}, f16x2);
+  const float ra = 2048.f * (a - (float)hv.x), rb = 2048.f * (b - (float)hv.y);
   h = __builtin_bit_cast(unsigned, hv);
   l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2v){ra, rb}, f16x2));
-}
-
-// 16 k-consecutive values of one row: two octets of the stage.
-__device__ __forceinline__ void split_store(const float (&x)[16], float s, float s11, char* d, int row, int part) {
-#pragma unroll
-  for (int o = 0; o < 2; ++o) {
-    unsigned h[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split_pair(x[8 * o + 2 * i], x[8 * o + 2 * i + 1], s, s11, h[i], l[i]);
-    char* q = d + (2 * part + o) * SP_OCT + row * 16;
-    *reinterpret_cast<uint4*>(q) = make_uint4(h[0], h[1], h[2], h[3]);
-    *reinterpret_cast<uint4*>(q + SP_PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
-  }
-}
-__device__ __forceinline__ float absmax16(const float (&x)[16]) {
-  float m = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
-  return m;
 }
 // Power-of-two scale that brings a value of magnitude m to [2^6, 2^7), as its exponent field.
 __device__ __forceinline__ int scale_field(float m) {
@@ -519,100 +511,209 @@ __device__ __forceinline__ int scale_field(float m) {
   return f > 254 ? 254 : f;
 }
 
-// Operand stored k-contiguous: thread q takes row q / 2, k-half q % 2.
+// Buffer loads of the staged operands: 32-bit offsets from the tile's (uniform) base, zero past `bytes`.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float* p, long long bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x00027000);
+}
+
+// One operand's stage registers.  load() issues the global loads of stage k; values() gives the
+// operand values of the stage loaded last; publish() and scales() choose the scales from the first stage's
+// values (a barrier lies between them) and store the exponents that undo them, ex[position]; store()
+// writes the planes.
+//
+// Operand stored k-contiguous: thread q takes k-quad q % 8 of rows q / 8 + 32 i, so that eight
+// lanes read one row's 128 bytes.  Rows past the end read the last one (their products are never stored).
 template <class L>
 struct SplitMK {
-  typename L::Raw raw[4];
-  __device__ __forceinline__ static int row(int tid) { return tid >> 1; }
-  __device__ __forceinline__ static int part(int tid) { return tid & 1; }
-  __device__ __forceinline__ void load(const L& ld, int r0, int r1, int k0, int K, int tid) {
-    const long long r = (long long)r0 + row(tid);
-    const long long rc = r < r1 ? r : (long long)r1 - 1;
-    const int k = k0 + 16 * part(tid), kc = k < K ? k : K - 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) raw[i] = ld.load(rc, kc + 4 * i);
-  }
-  // Returns the factor of the values: past K (a last stage of 16 k) they repeat the last ones and count 0 times.
-  __device__ __forceinline__ float values(const L& ld, int k0, int K, int tid, float (&x)[16]) const {
-    const int k = k0 + 16 * part(tid), kc = k < K ? k : K - 16;
+  static constexpr bool kPaired = false;   // position of row m in the tile: m
+  using Values = float4[4];
+  const L& ld;
+  __amdgpu_buffer_rsrc_t rs;
+  int vo[4];
+  float4 raw[4];
+  float s[4];
+  __device__ __forceinline__ SplitMK(const L& l, int r0, int r1, int, int, int tid) : ld(l) {
+    const int n = r1 - r0 < GBM ? r1 - r0 : GBM;
+    rs = buffer_of(l.base() + (long long)r0 * l.ld, 4LL * n * l.ld);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float4 v = ld.apply(raw[i], kc + 4 * i);
-      x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+      const int r = (tid >> 3) + 32 * i;
+      vo[i] = 4 * ((r < n ? r : n - 1) * (int)l.ld + 4 * (tid & 7));
     }
-    return k < K ? 1.f : 0.f;
+  }
+  __device__ __forceinline__ void load(int k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      raw[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[i], 4 * k, 0));
+  }
+  __device__ __forceinline__ void values(int k, int tid, Values& x) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = ld.apply(raw[i], k + 4 * (tid & 7));
+  }
+  __device__ __forceinline__ static void publish(const Values&, float*, int) {}
+  __device__ __forceinline__ void scales(const Values& x, const float*, int* ex, int tid) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float m = fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+      const int f = scale_field(m);
+      s[i] = __uint_as_float((unsigned)f << 23);
+      if ((tid & 7) == 0) ex[(tid >> 3) + 32 * i] = 127 - f;
+    }
+  }
+  // a quarter of the stage: values, planes, and the loads of the stage that follows
+  __device__ __forceinline__ void store(int i, float4 x, char* d, int tid) const {
+    const int kq = tid & 7;
+    d += (kq >> 1) * SP_OCT + ((tid >> 3) + 32 * i) * 16 + (kq & 1) * 8;
+    unsigned h[2], l[2];
+    split_pair(x.x, x.y, s[i], h[0], l[0]);
+    split_pair(x.z, x.w, s[i], h[1], l[1]);
+    *reinterpret_cast<uint2*>(d) = make_uint2(h[0], h[1]);
+    *reinterpret_cast<uint2*>(d + SP_PLANE) = make_uint2(l[0], l[1]);
+  }
+  __device__ __forceinline__ void piece(int i, int k, int next, char* d, int tid) {
+    store(i, ld.apply(raw[i], k + 4 * (tid & 7)), d, tid);
+    raw[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[i], 4 * next, 0));
+  }
+  __device__ __forceinline__ void store_all(const Values& x, char* d, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store(i, x[i], d, tid);
   }
 };
 
-// Operand stored row-contiguous ([k][m]): thread q takes column q % 128 of the 16 k-rows of half
-// q / 128 (one half per wave).  Rows past rk_end count as zeros; columns past m_end read the last
-// one (their products are never stored).
+// Operand stored row-contiguous ([k][m]): wave w takes the eight k-rows of octet w and lane q its
+// columns 2 q and 2 q + 1, so that a load reads a whole 512-byte row of the tile.  Even columns of a
+// 64-column half go to its first 32 positions, odd ones to the last (each lane's store is then next
+// to its neighbour's).  k-rows past the end are zeros; columns past m_end read the last pair.
 template <class L>
 struct SplitKM {
-  typename L::Raw1 raw[16];
-  __device__ __forceinline__ static int row(int tid) { return tid & 127; }
-  __device__ __forceinline__ static int part(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 7); }
-  __device__ __forceinline__ void load(const L& ld, long long rk, long long rk_end, int m0, int m_end, int tid) {
-    const int m = m0 + row(tid), mc = m < m_end ? m : m_end - 1;
-    const long long r = rk + 16 * part(tid);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) raw[i] = ld.load1(r + i < rk_end ? r + i : rk_end - 1, mc);
+  static constexpr bool kPaired = true;
+  using Values = float2[8];
+  const L& ld;
+  __amdgpu_buffer_rsrc_t rs;
+  int vo, mc, kb, ke;
+  unsigned h[4], l[4];
+  float2 raw[8];
+  float s[2];
+  __device__ __forceinline__ static int pos(int lane, int j) { return ((lane & 32) << 1) | (j << 5) | (lane & 31); }
+  __device__ __forceinline__ static int octet(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
+  __device__ __forceinline__ SplitKM(const L& l, int m0, int m_end, int kb_, int ke_, int tid)
+      : ld(l), kb(kb_), ke(ke_) {
+    rs = buffer_of(l.base() + (long long)kb_ * l.ld, 4LL * (ke_ - kb_) * l.ld);
+    const int m = m0 + 2 * (tid & 63);
+    mc = m < m_end ? m : m_end - 2;
+    vo = 4 * (8 * octet(tid) * (int)l.ld + mc);
   }
-  __device__ __forceinline__ float values(const L& ld, long long rk, long long rk_end, int m0, int m_end, int tid,
-                                          float (&x)[16]) const {
-    const int m = m0 + row(tid), mc = m < m_end ? m : m_end - 1;
-    const long long left = rk_end - (rk + 16 * part(tid));
+  __device__ __forceinline__ void load_rows(int k, int i0, int n) {
+    const int row = 4 * (int)ld.ld, at = vo + (k - kb) * row;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = ld.apply1(raw[i], mc);
-    if (left < 16) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) x[i] = i < left ? x[i] : 0.f;
+    for (int i = i0; i < i0 + n; ++i)
+      raw[i] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, at + i * row, 0, 0));
+  }
+  __device__ __forceinline__ void load(int k) { load_rows(k, 0, 8); }
+  __device__ __forceinline__ float2 value(int i, int k, int tid) const {
+    float f = 1.f;
+    if constexpr (L::kRowFactor) {
+      const int r = k + 8 * octet(tid) + i;
+      f = ld.s[r < ke ? r : ke - 1];
     }
-    return 1.f;
+    return ld.apply2(raw[i], f, mc);
+  }
+  __device__ __forceinline__ void values(int k, int tid, Values& x) const {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = value(i, k, tid);
+  }
+  __device__ __forceinline__ static void publish(const Values& x, float* mx, int tid) {
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      a = fmaxf(a, fabsf(x[i].x));
+      b = fmaxf(b, fabsf(x[i].y));
+    }
+    reinterpret_cast<float2*>(mx)[tid] = make_float2(a, b);
+  }
+  __device__ __forceinline__ void scales(const Values&, const float* mx, int* ex, int tid) {
+    const int lane = tid & 63;
+    float m[2] = {0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float2 v = reinterpret_cast<const float2*>(mx)[w * 64 + lane];
+      m[0] = fmaxf(m[0], v.x);
+      m[1] = fmaxf(m[1], v.y);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int f = scale_field(m[j]);
+      s[j] = __uint_as_float((unsigned)f << 23);
+      if (tid < 64) ex[pos(lane, j)] = 127 - f;
+    }
+  }
+  __device__ __forceinline__ void put(int j, char* d, int tid) const {
+    d += octet(tid) * SP_OCT + pos(tid & 63, j) * 16;
+    *reinterpret_cast<uint4*>(d) = make_uint4(h[0], h[1], h[2], h[3]);
+    *reinterpret_cast<uint4*>(d + SP_PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
+  }
+  // a quarter of the stage: one column of each pair, four k; and the loads of the stage that follows
+  __device__ __forceinline__ void piece(int n, int k, int next, char* d, int tid) {
+    const int j = n >> 1, i0 = 4 * (n & 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float2 u = value(i0 + 2 * i, k, tid), v = value(i0 + 2 * i + 1, k, tid);
+      split_pair(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i0 / 2 + i], l[i0 / 2 + i]);
+    }
+    if (n & 1) put(j, d, tid);
+    if (j) load_rows(next, i0, 4);
+  }
+  __device__ __forceinline__ void store_all(const Values& x, char* d, int tid) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float2 u = x[2 * i], v = x[2 * i + 1];
+        split_pair(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i], l[i]);
+      }
+      put(j, d, tid);
+    }
   }
 };
 
-// One stage of split products: per 32 x 32 block and 16 k, hi += h h and lo += h l + l h.
+// One stage of split products: per 32 x 32 block and 16 k, hi += h h' and lo += h l' + l h'.  After
+// every third of the 24 matrix instructions piece(0..7) runs: the conversion of the next stage in
+// eight parts, spread so that the vector units work while the matrix unit does.
+template <class F>
 __device__ __forceinline__ void split_stage(const char* st, int wm, int wn, int lr, int hf, f32x16 (&hi)[2][2],
-                                            f32x16 (&lo)[2][2]) {
+                                            f32x16 (&lo)[2][2], const F& piece) {
+  f16x8 a[2][2], b[2][2];
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    f16x8 a[2][2], b[2][2];
+  for (int q = 0; q < 24; ++q) {
+    const int g = q / 12, t = q / 4 % 3, bi = q / 2 % 2, bj = q % 2;
+    if (q % 12 == 0) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+      for (int p = 0; p < 2; ++p)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const char* o = st + p * SP_PLANE + (2 * g + hf) * SP_OCT;
-        a[q][p] = *reinterpret_cast<const f16x8*>(o + (wm * 64 + q * 32 + lr) * 16);
-        b[q][p] = *reinterpret_cast<const f16x8*>(o + SP_OPER + (wn * 64 + q * 32 + lr) * 16);
-      }
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj)
-        hi[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][0], hi[bi][bj], 0, 0, 0);
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj)
-        lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][1], lo[bi][bj], 0, 0, 0);
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj)
-        lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][1], b[bj][0], lo[bi][bj], 0, 0, 0);
+        for (int c = 0; c < 2; ++c) {
+          const char* o = st + p * SP_PLANE + (2 * g + hf) * SP_OCT;
+          a[c][p] = *reinterpret_cast<const f16x8*>(o + (wm * 64 + c * 32 + lr) * 16);
+          b[c][p] = *reinterpret_cast<const f16x8*>(o + SP_OPER + (wn * 64 + c * 32 + lr) * 16);
+        }
+    }
+    if (t == 0)
+      hi[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][0], hi[bi][bj], 0, 0, 0);
+    else
+      lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][t == 2], b[bj][t == 1], lo[bi][bj], 0, 0, 0);
+    if (q % 3 == 2) piece(q / 3);
   }
 }
 
-// The K loop of the split products over [kb, ke): la / lb load one stage's registers, va / vb
-// give their values and the factor of these.  On return hi holds h h' + 2^-11 (h l' + l h') of the
-// scaled operands and smem the exponents that undo the scales; false if a value is not finite.
-// Bound by the LDS traffic (64 KB read and 32 KB written per stage against 768 matrix cycles) and by
-// the clock that the matrix units leave; two workgroups per CU (about 210 registers) overlap one's
-// conversions and barriers with the other's products.
-template <class SA, class SB, class LA, class LB, class VA, class VB>
-__device__ __forceinline__ bool split_loop(float* smem, long long kb, long long ke, const LA& la, const LB& lb,
-                                           const VA& va, const VB& vb, int wm, int wn, int lr, int hf, int tid,
+// The K loop of the split products over [kb, ke).  A and B: loader, first and last row (column)
+// of the tile's operand.  On return hi holds h h' + 2^-11 (h l' + l h') of the scaled operands and
+// smem the exponents that undo the scales; false if a value is not finite.
+template <class SA, class SB, class LA, class LB>
+__device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, int a1, const LB& bl, int b0, int b1,
+                                           int kb, int ke, int wm, int wn, int lr, int hf, int tid,
                                            f32x16 (&hi)[2][2]) {
   char* lds = reinterpret_cast<char*>(smem);
   int* ex = reinterpret_cast<int*>(smem + SMEM_BODY);   // [128] rows, [128] columns
@@ -620,52 +721,45 @@ __device__ __forceinline__ bool split_loop(float* smem, long long kb, long long 
   f32x16 lo[2][2];
   zero_acc(hi);
   zero_acc(lo);
-  SA sa;
-  SB sb;
-  float s_a, s_b, s11_a, s11_b;
+  SA sa(al, a0, a1, kb, ke, tid);
+  SB sb(bl, b0, b1, kb, ke, tid);
+  sa.load(kb);
+  sb.load(kb);
   {
-    // scales from the first stage's largest magnitudes per row and per column
-    float xa[16], xb[16];
-    la(sa, kb);
-    lb(sb, kb);
-    const float ca = va(sa, kb, xa), cb = vb(sb, kb, xb);
-    float* mx = smem + SP_STAGE / 4;   // [2 operands][2 parts][128], in the second stage buffer
-    mx[SA::part(tid) * 128 + SA::row(tid)] = absmax16(xa);
-    mx[256 + SB::part(tid) * 128 + SB::row(tid)] = absmax16(xb);
-    __syncthreads();
-    const int fa = scale_field(fmaxf(mx[SA::row(tid)], mx[128 + SA::row(tid)]));
-    const int fb = scale_field(fmaxf(mx[256 + SB::row(tid)], mx[384 + SB::row(tid)]));
-    s_a = __uint_as_float((unsigned)fa << 23);
-    s_b = __uint_as_float((unsigned)fb << 23);
-    s11_a = s_a * 2048.f;
-    s11_b = s_b * 2048.f;
-    ex[SA::row(tid)] = 127 - fa;
-    ex[128 + SB::row(tid)] = 127 - fb;
-    split_store(xa, ca * s_a, ca * s11_a, lds, SA::row(tid), SA::part(tid));
-    split_store(xb, cb * s_b, cb * s11_b, lds + SP_OPER, SB::row(tid), SB::part(tid));
+    typename SA::Values xa;
+    typename SB::Values xb;
+    sa.values(kb, tid, xa);
+    sb.values(kb, tid, xb);
+    float* mx = smem + SP_STAGE / 4;   // the second stage buffer, not in use yet
+    sa.publish(xa, mx, tid);
+    sb.publish(xb, mx + 512, tid);
+    if constexpr (SA::kPaired || SB::kPaired) __syncthreads();
+    sa.scales(xa, mx, ex, tid);
+    sb.scales(xb, mx + 512, ex + GBM, tid);
+    sa.store_all(xa, lds, tid);
+    sb.store_all(xb, lds + SP_OPER, tid);
   }
+  // The registers run one stage ahead of the planes: while stage k is multiplied, stage k + 1 (whose
+  // loads were issued a whole stage earlier) is converted and the loads of stage k + 2 are issued.
+  const int last = kb + (ke - kb - 1) / SBK * SBK;
+  int k1 = kb + SBK < last ? kb + SBK : last;
+  sa.load(k1);
+  sb.load(k1);
   __syncthreads();
   int cur = 0;
-  for (long long k = kb; k < ke; k += SBK) {
-    const bool more = k + SBK < ke;
-    if (more) {
-      la(sa, k + SBK);
-      lb(sb, k + SBK);
-    }
-    __builtin_amdgcn_s_setprio(1);
-    split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo);
-    __builtin_amdgcn_s_setprio(0);
-    if (more) {
-      char* d = lds + (cur ^ 1) * SP_STAGE;
-      float x[16];
-      const float ca = va(sa, k + SBK, x);
-      split_store(x, ca * s_a, ca * s11_a, d, SA::row(tid), SA::part(tid));
-      const float cb = vb(sb, k + SBK, x);
-      split_store(x, cb * s_b, cb * s11_b, d + SP_OPER, SB::row(tid), SB::part(tid));
-    }
+  for (int k = kb; k < last; k += SBK) {
+    char* d = lds + (cur ^ 1) * SP_STAGE;
+    const int next = k1 + SBK < last ? k1 + SBK : last;
+    split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [&](int n) {
+      if (n < 4) sa.piece(n, k1, next, d, tid); else sb.piece(n - 4, k1, next, d + SP_OPER, tid);
+      __builtin_amdgcn_sched_barrier(0);   // keeps the parts where they are
+    });
+    k1 = next;
     __syncthreads();
     cur ^= 1;
   }
+  split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [](int) {});
+  __syncthreads();
   float z = 0.f;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -757,17 +851,8 @@ __device__ __forceinline__ bool rows_split(float* smem, const ALoad& al, const f
                                            int r0, int r1, int n0, int wm, int wn, int lr, int hf, int tid,
                                            f32x16 (&acc)[2][2]) {
   const LoadPlain bl{Bg, NT ? K : N};
-  using SA = SplitMK<ALoad>;
   using SB = std::conditional_t<NT, SplitMK<LoadPlain>, SplitKM<LoadPlain>>;
-  auto la = [&](SA& x, long long k) { x.load(al, r0, r1, (int)k, K, tid); };
-  auto va = [&](const SA& x, long long k, float (&v)[16]) { return x.values(al, (int)k, K, tid, v); };
-  auto lb = [&](SB& x, long long k) {
-    if constexpr (NT) x.load(bl, n0, N, (int)k, K, tid); else x.load(bl, k, K, n0, N, tid);
-  };
-  auto vb = [&](const SB& x, long long k, float (&v)[16]) {
-    if constexpr (NT) return x.values(bl, (int)k, K, tid, v); else return x.values(bl, k, K, n0, N, tid, v);
-  };
-  if (!split_loop<SA, SB>(smem, 0, K, la, lb, va, vb, wm, wn, lr, hf, tid, acc)) return false;
+  if (!split_loop<SplitMK<ALoad>, SB>(smem, al, r0, r1, bl, n0, N, 0, K, wm, wn, lr, hf, tid, acc)) return false;
   unscale(smem, wm, wn, lr, hf, acc);
   return true;
 }
@@ -794,9 +879,11 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
   const int lr = l & 31, hf = l >> 5;
 
   f32x16 acc[2][2];
+  bool paired = false;   // columns of the two blocks: 2 lr and 2 lr + 1 (else lr and 32 + lr)
   if constexpr (Split) {
-    if (!rows_split<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc))
-      rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+    paired = rows_split<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+    if (!paired) rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+    paired = paired && !NT;
   } else {
     rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
   }
@@ -815,7 +902,8 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            sC[(bi * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)) * LD_C + wn * 64 + bj * 32 + lr] = acc[bi][bj][v];
+            sC[(bi * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)) * LD_C + wn * 64 + (paired ? 2 * lr + bj : bj * 32 + lr)] =
+                acc[bi][bj][v];
     }
     // 4 pieces per batch; loads past the range read the last valid row.
     const int c4 = tid & 31;
@@ -925,13 +1013,8 @@ template <class ALoad, class BLoad>
 __device__ __forceinline__ bool wgrad_split(float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
                                             const WChunk& ch, int p0, int q0, int wm, int wn, int lr, int hf, int tid,
                                             f32x16 (&acc)[2][2]) {
-  using SA = SplitKM<ALoad>;
-  using SB = SplitKM<BLoad>;
-  auto la = [&](SA& x, long long k) { x.load(al, k, ch.r1, p0, P, tid); };
-  auto va = [&](const SA& x, long long k, float (&v)[16]) { return x.values(al, k, ch.r1, p0, P, tid, v); };
-  auto lb = [&](SB& x, long long k) { x.load(bl, k, ch.r1, q0, Q, tid); };
-  auto vb = [&](const SB& x, long long k, float (&v)[16]) { return x.values(bl, k, ch.r1, q0, Q, tid, v); };
-  if (!split_loop<SA, SB>(smem, ch.r0, ch.r1, la, lb, va, vb, wm, wn, lr, hf, tid, acc)) return false;
+  if (!split_loop<SplitKM<ALoad>, SplitKM<BLoad>>(smem, al, p0, P, bl, q0, Q, ch.r0, ch.r1, wm, wn, lr, hf, tid, acc))
+    return false;
   unscale(smem, wm, wn, lr, hf, acc);
   return true;
 }
@@ -955,9 +1038,10 @@ __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoa
   const int lr = l & 31, hf = l >> 5;
 
   f32x16 acc[2][2];
+  bool paired = false;   // rows and columns of the two blocks: 2 i and 2 i + 1 (else i and 32 + i)
   if constexpr (Split) {
-    if (!wgrad_split(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc))
-      wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
+    paired = wgrad_split(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
+    if (!paired) wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
   } else {
     wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
   }
@@ -966,12 +1050,19 @@ __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoa
 #pragma unroll
   for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-    for (int bj = 0; bj < 2; ++bj) {
-      const int qc = q0 + wn * 64 + bj * 32 + lr;
+    for (int v = 0; v < 16; ++v) {
+      const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
+      const int pr = p0 + wm * 64 + (paired ? 2 * i + bi : bi * 32 + i);
+      if (paired) {
+        const int qc = q0 + wn * 64 + 2 * lr;
+        if (pr < P && qc < Q)
+          *reinterpret_cast<float2*>(out + (long long)pr * Q + qc) = make_float2(acc[bi][0][v], acc[bi][1][v]);
+      } else {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int pr = p0 + wm * 64 + bi * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
-        if (pr < P && qc < Q) out[(long long)pr * Q + qc] = acc[bi][bj][v];
+        for (int bj = 0; bj < 2; ++bj) {
+          const int qc = q0 + wn * 64 + bj * 32 + lr;
+          if (pr < P && qc < Q) out[(long long)pr * Q + qc] = acc[bi][bj][v];
+        }
       }
     }
 }

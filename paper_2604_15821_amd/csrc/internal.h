@@ -160,13 +160,23 @@ void launch_wgrad_reduce(hipStream_t st, const float* partial, const int* chunk_
 using Fp32Only = std::false_type;
 constexpr Fp32Only kFp32{};
 
+// What the split products take: whole stages of K, and operand tiles within the 32-bit offsets
+// of buffer loads (the tile's first row to its last, and one stage past it).  Anything else is
+// multiplied on the fp32 instructions.
+inline bool split_takes_rows(int K, int N) {
+  return K % SBK == 0 && 4LL * K * GBM <= INT32_MAX && 4LL * (K + 2 * SBK) * N <= INT32_MAX;
+}
+inline bool split_takes_wgrad(int P, int Q) {   // chunks are at most 2048 rows
+  return 4LL * (2048 + 2 * SBK) * (P > Q ? P : Q) <= INT32_MAX;
+}
+
 template <bool NT, class S, class ALoad, class Epi>
 void launch_rows(S split, hipStream_t st, const ALoad& al, const float* B, int K, int N, const RowsTile* tiles,
                  const int* n_tiles, int max_tiles, const Epi& epi, float* rowsum = nullptr) {
   if (max_tiles <= 0) return;
   dim3 grid(xcd_grid(max_tiles, (N + GBN - 1) / GBN));
   if constexpr (!std::is_same_v<S, Fp32Only>) {
-    if (split) {
+    if (split && split_takes_rows(K, N)) {
       hipLaunchKernelGGL((gemm_rows_kernel<NT, ALoad, Epi, true>), grid, dim3(256), 0, st, al, B, K, N, tiles,
                          n_tiles, epi, rowsum);
       return;
@@ -184,7 +194,7 @@ void launch_wgrad(S split, hipStream_t st, const ALoad& al, const BLoad& bl, int
     dim3 grid(xcd_grid(max_chunks, ((P + GBM - 1) / GBM) * ((Q + GBN - 1) / GBN)));
     bool launched = false;
     if constexpr (!std::is_same_v<S, Fp32Only>) {
-      if (split) {
+      if (split && split_takes_wgrad(P, Q)) {
         hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad, true>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
                            n_chunks, partial);
         launched = true;
