@@ -20,6 +20,13 @@ __device__ __forceinline__ void image_range(const float* L, float rc, int& mx, i
   mz = (int)floor((double)rc / (double)L[8]) + 1;
 }
 
+// All-pairs candidates n_s * n_images from which a structure may use the cell list in mode 0.  The whole
+// build at r_cut = 6 and 27 images, all pairs against cell list: 536 and 865 us for 32 structures of 1200
+// atoms, 1169 and 1425 for 32 of 2048, 248 and 284 for 4 of 2048, 535 and 327 for 2 of 5000; the
+// line lies at 3034 atoms of 27 images.
+constexpr long long kCellMinCand = 81920;
+
+// Flag bits: 1 bad offsets, 2 unsupported cell, 32 (with rc > 0) a structure that may use the cell list.
 __global__ void validate_struct_kernel(const int* __restrict__ offsets, int S, int N, const float* __restrict__ cell,
                                        float rc, int* __restrict__ flag) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -35,6 +42,12 @@ __global__ void validate_struct_kernel(const int* __restrict__ offsets, int S, i
       if (!(L[0] > 0.f) || !(L[4] > 0.f) || !(L[8] > 0.f)) bad |= 2;
       // image shifts are stored as int8 and the candidate count must stay small
       else if ((double)rc / L[0] > 60.0 || (double)rc / L[4] > 60.0 || (double)rc / L[8] > 60.0) bad |= 2;
+      else if (!(bad & 1)) {
+        int mx, my, mz;
+        image_range(L, rc, mx, my, mz);
+        const long long nimg = (long long)(2 * mx + 1) * (2 * my + 1) * (2 * mz + 1);
+        if ((long long)(offsets[s + 1] - offsets[s]) * nimg >= kCellMinCand) bad |= 32;
+      }
     }
   }
   if (bad) atomicOr(flag, bad);
@@ -81,69 +94,118 @@ struct CellGrid {
 // with more neighbours is written by the all-pairs kernel instead.
 constexpr int kCellCap = 512;
 
-// One wave per centre atom; candidates (j, image) are tested 64 at a time in
-// canonical order and compacted with a ballot, so the output order is exact.
-// Centres of structures that use the cell list are skipped (the write pass
-// takes those whose neighbours exceed kCellCap).
+// All-pairs search: one wave per centre atom, one neighbour atom j per lane, every image of j
+// tested by its lane.  The cell is diagonal (validated before), so the shift of image (ix, iy, iz) is
+// (ix Lx, iy Ly, iz Lz) exactly as image_shift rounds it, and r2 = (dx^2 + dy^2) + dz^2 grows
+// with each term also when every operation is rounded: an ix (iy) whose dx^2 (dx^2 + dy^2) is not
+// below rc^2 has no image to test.  Lanes hold consecutive j and each lists its images in order, so
+// an exclusive scan of the lanes' counts gives the canonical order.
+// Bound by the vector units.  With candidates (j, image) dealt to lanes and taken apart by 64-bit
+// divisions, 256 structures of 8-512 atoms (2.1 M edges, r_cut 6) took 647 us to count and 687 us to
+// write; now 44 and 65.
+// Centres of structures that use the cell list are skipped (the write pass takes those whose
+// neighbours exceed kCellCap).
 template <bool WRITE>
 __global__ void nl_kernel(const float* __restrict__ pos, const float* __restrict__ cell,
                           const int* __restrict__ offsets, const int* __restrict__ sid, float rc, int N,
                           int* __restrict__ count, const int* __restrict__ rowptr, int* __restrict__ ei,
-                          int* __restrict__ ej, int8_t* __restrict__ shift, const CellGrid* __restrict__ grid) {
-  const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+                          int* __restrict__ ej, int8_t* __restrict__ shift, int* __restrict__ rev,
+                          const CellGrid* __restrict__ grid) {
+  const int i = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
   const int s = sid[i];
-  if (grid[s].use && (!WRITE || count[i] <= kCellCap)) return;
+  if (grid && grid[s].use && (!WRITE || count[i] <= kCellCap)) return;
   const int a = offsets[s], n = offsets[s + 1] - a;
   const float* L = cell + 9 * s;
+  const float Lx = L[0], Ly = L[4], Lz = L[8];
   int mx, my, mz;
   image_range(L, rc, mx, my, mz);
-  const int ny = 2 * my + 1, nz = 2 * mz + 1;
-  const int nimg = (2 * mx + 1) * ny * nz;
   const float xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
   const float rc2 = __fmul_rn(rc, rc);
-  const long long ncand = (long long)n * nimg;
-  const int base = WRITE ? rowptr[i] : 0;
+  const int ny = 2 * my + 1, nz = 2 * mz + 1;
+  const int packed = ((lane / (ny * nz) - mx) & 255) | ((((lane / nz) % ny - my) & 255) << 8) | ((lane % nz - mz) << 16);
+  int base = WRITE ? rowptr[i] : 0;
   int cnt = 0;
-  for (long long c0 = 0; c0 < ncand; c0 += 64) {
-    const long long c = c0 + lane;
-    bool keep = false;
-    int j = 0, ix = 0, iy = 0, iz = 0;
-    if (c < ncand) {
-      j = a + (int)(c / nimg);
-      const int im = (int)(c % nimg);
-      ix = im / (ny * nz) - mx;
-      iy = (im / nz) % ny - my;
-      iz = im % nz - mz;
-      float sx, sy, sz;
-      image_shift(L, ix, iy, iz, sx, sy, sz);
-      keep = pair_kept(pos, i, j, xi, yi, zi, sx, sy, sz, ix == 0 && iy == 0 && iz == 0, rc2);
+  for (int j0 = 0; j0 < n; j0 += 64) {
+    const bool live = j0 + lane < n;
+    const int j = live ? a + j0 + lane : i;
+    const float bx = __fsub_rn(pos[3 * j], xi), by = __fsub_rn(pos[3 * j + 1], yi), bz = __fsub_rn(pos[3 * j + 2], zi);
+    // f(image) for every image of j within the cutoff, in order
+    auto images = [&](auto f) {
+      for (int ix = -mx; ix <= mx; ++ix) {
+        const float dx = __fadd_rn(bx, __fmul_rn((float)ix, Lx)), dx2 = __fmul_rn(dx, dx);
+        const bool inx = live && dx2 < rc2;
+        if (!__any(inx)) continue;
+        for (int iy = -my; iy <= my; ++iy) {
+          const float dy = __fadd_rn(by, __fmul_rn((float)iy, Ly)), s2 = __fadd_rn(dx2, __fmul_rn(dy, dy));
+          const bool iny = inx && s2 < rc2;
+          if (!__any(iny)) continue;
+          for (int iz = -mz; iz <= mz; ++iz) {
+            const float dz = __fadd_rn(bz, __fmul_rn((float)iz, Lz));
+            const bool self = j == i && ix == 0 && iy == 0 && iz == 0;
+            f(iny && __fadd_rn(s2, __fmul_rn(dz, dz)) < rc2 && !self, ix, iy, iz);
+          }
+        }
+      }
+    };
+    int c = 0;
+    unsigned kept = 0;   // with at most 32 images: bit of every kept one
+    images([&](bool keep, int ix, int iy, int iz) {
+      c += keep;
+      if (WRITE) kept |= (unsigned)keep << ((((ix + mx) * ny + iy + my) * nz + iz + mz) & 31);
+    });
+    if (!WRITE) {
+      cnt += c;
+      continue;
     }
-    const unsigned long long m = __ballot(keep);
-    if (WRITE && keep) {
-      const int p = base + cnt + __popcll(m & ((1ull << lane) - 1ull));
+    int pre = c;   // inclusive scan over the lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(pre, o, 64);
+      if (lane >= o) pre += v;
+    }
+    int p = base + pre - c;
+    auto put = [&](int ix, int iy, int iz) {
       ei[p] = i;
       ej[p] = j;
-      shift[3 * p] = (int8_t)ix;
-      shift[3 * p + 1] = (int8_t)iy;
-      shift[3 * p + 2] = (int8_t)iz;
+      rev[p] = p;
+      shift[3LL * p] = (int8_t)ix;
+      shift[3LL * p + 1] = (int8_t)iy;
+      shift[3LL * p + 2] = (int8_t)iz;
+      ++p;
+    };
+    if ((2 * mx + 1) * ny * nz <= 32) {
+      while (__any(kept != 0)) {
+        // lane q holds image q, packed
+        const int img = __shfl(packed, kept ? __builtin_ctz(kept) : 0, 64);
+        if (kept) put((int8_t)img, (int8_t)(img >> 8), (int8_t)(img >> 16));
+        kept &= kept - 1;
+      }
+    } else {
+      images([&](bool keep, int ix, int iy, int iz) {
+        if (keep) put(ix, iy, iz);
+      });
     }
-    cnt += __popcll(m);
+    base += __shfl(pre, 63, 64);
   }
-  if (!WRITE && lane == 0) count[i] = cnt;
+  if (!WRITE) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    if (lane == 0) count[i] = cnt;
+  }
 }
 
 // ------------------------------------------------------------------ cell list
 // A structure uses the cell list when mode says so (1: every structure, 2:
 // none) or, in mode 0, when its all-pairs candidate count n_s * n_images is at
-// least kCellMinCand and its box holds at least 27 bins.  Bins are built per
+// least kCellMinCand and its box holds at least 27 bins; without any structure of that
+// size the cell-list kernels are not launched.  Bins are built per
 // structure from the atoms' own bounding box (positions need not be wrapped);
 // a centre then tests, for every image n, only the atoms of the bins that the
 // ball of radius r_cut around X_i - s(n) reaches, with the same fp32 test, and
 // its kept (j, n) are sorted into the canonical order in LDS: the list is
 // bitwise the all-pairs one.
-constexpr long long kCellMinCand = 32768;
 
 // One workgroup per structure: bounding box, bins, use flag; nbins[s] = bins used.
 __global__ void cell_grid_kernel(const float* __restrict__ pos, const float* __restrict__ cell,
@@ -256,7 +318,8 @@ __global__ __launch_bounds__(256) void nl_cell_kernel(
     const float* __restrict__ pos, const float* __restrict__ cell, const int* __restrict__ offsets,
     const int* __restrict__ sid, float rc, int N, const CellGrid* __restrict__ grid, const int* __restrict__ bin_off,
     const int* __restrict__ bstart, const int* __restrict__ batoms, int* __restrict__ count,
-    const int* __restrict__ rowptr, int* __restrict__ ei, int* __restrict__ ej, int8_t* __restrict__ shift) {
+    const int* __restrict__ rowptr, int* __restrict__ ei, int* __restrict__ ej, int8_t* __restrict__ shift,
+    int* __restrict__ rev) {
   __shared__ unsigned long long keys_all[4][kCellCap];
   const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
@@ -336,6 +399,7 @@ __global__ __launch_bounds__(256) void nl_cell_kernel(
     const int im = (int)(k % (unsigned long long)nimg);
     ei[p] = i;
     ej[p] = j;
+    rev[p] = p;
     shift[3 * p] = (int8_t)(im / (ny * nz) - mx);
     shift[3 * p + 1] = (int8_t)((im / nz) % ny - my);
     shift[3 * p + 2] = (int8_t)(im % nz - mz);
@@ -362,6 +426,60 @@ __device__ __forceinline__ long long block_exclusive_scan(long long v, long long
   const long long r = part[t] - v;
   __syncthreads();
   return r;
+}
+
+// The same by one workgroup, for inputs of up to kScanOne values: one launch in place of three
+// (a launch of these takes 3 to 5 us whatever its size; 32 262 values: SCAN_FIG).
+constexpr int kScanOneThreads = 1024, kScanOne = 65536;
+__global__ __launch_bounds__(kScanOneThreads) void scan_one_kernel(const int* __restrict__ in, int n,
+                                                                   int* __restrict__ out, int* __restrict__ flag) {
+  __shared__ long long wsum[kScanOneThreads / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  long long carry = 0;
+  constexpr int kPer = 16;
+  for (int i0 = 0; i0 < n; i0 += kPer * kScanOneThreads) {
+    const int i = i0 + kPer * t;
+    int v[kPer];
+    long long s = 0;
+    if (i + kPer <= n) {
+#pragma unroll
+      for (int k = 0; k < kPer; k += 4) {
+        const int4 u = *reinterpret_cast<const int4*>(in + i + k);
+        v[k] = u.x; v[k + 1] = u.y; v[k + 2] = u.z; v[k + 3] = u.w;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) v[k] = i + k < n ? in[i + k] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) s += v[k];
+    long long inc = s;   // inclusive scan over the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const long long u = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += u;
+    }
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    long long before = carry, total = 0;
+#pragma unroll
+    for (int q = 0; q < kScanOneThreads / 64; ++q) {
+      if (q < w) before += wsum[q];
+      total += wsum[q];
+    }
+    long long run = before + inc - s;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (i + k < n) out[i + k] = (int)run;
+      run += v[k];
+    }
+    carry += total;
+    __syncthreads();
+  }
+  if (t == 0) {
+    out[n] = (int)carry;
+    if (carry > 0x7fffffffLL && flag) atomicOr(flag, 16);
+  }
 }
 
 __global__ void scan_tile_sums_kernel(const int* __restrict__ in, int n, long long* __restrict__ sums) {
@@ -416,32 +534,42 @@ __global__ void scan_tile_kernel(const int* __restrict__ in, int n, const long l
   }
 }
 
-// rev[e] = the edge (j, i, -n), found by binary search in the sorted segment of j.
+// rev[e] = the edge (j, i, -n), found by binary search in the sorted segment of j.  Bound by the
+// scattered loads of the search, so only one edge of a pair searches (i < j, or i = j and the first
+// non-zero shift positive) and writes both entries; the write pass has left rev[e] = e, which an edge
+// without a partner keeps (flag bit 8).  2.1 M edges: 87 us with every edge searching, now 55.
 __global__ void reverse_kernel(const int* __restrict__ ei, const int* __restrict__ ej,
                                const int8_t* __restrict__ shift, const int* __restrict__ rowptr, int Ne,
                                int* __restrict__ rev, int* __restrict__ flag) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= Ne) return;
   const int i = ei[e], j = ej[e];
-  const int kx = -shift[3 * e], ky = -shift[3 * e + 1], kz = -shift[3 * e + 2];
+  if (i > j) return;
+  const int kx = -shift[3LL * e], ky = -shift[3LL * e + 1], kz = -shift[3LL * e + 2];
+  if (i == j && (kx != 0 ? kx > 0 : ky != 0 ? ky > 0 : kz > 0)) return;
   // key of an edge within the segment of j: (ej, sx, sy, sz) lexicographic
   auto less = [&](int f) {
     int fj = ej[f];
     if (fj != i) return fj < i;
-    int fx = shift[3 * f], fy = shift[3 * f + 1], fz = shift[3 * f + 2];
+    int fx = shift[3LL * f], fy = shift[3LL * f + 1], fz = shift[3LL * f + 2];
     if (fx != kx) return fx < kx;
     if (fy != ky) return fy < ky;
     return fz < kz;
   };
   int lo = rowptr[j], hi = rowptr[j + 1];
+  const int end = hi;
   while (lo < hi) {
     int mid = (lo + hi) >> 1;
     if (less(mid)) lo = mid + 1; else hi = mid;
   }
-  bool ok = lo < rowptr[j + 1] && ej[lo] == i && shift[3 * lo] == kx && shift[3 * lo + 1] == ky &&
-            shift[3 * lo + 2] == kz;
-  rev[e] = ok ? lo : e;
-  if (!ok) atomicOr(flag, 8);
+  const bool ok = lo < end && ej[lo] == i && shift[3LL * lo] == kx && shift[3LL * lo + 1] == ky &&
+                  shift[3LL * lo + 2] == kz;
+  if (ok) {
+    rev[e] = lo;
+    rev[lo] = e;
+  } else {
+    atomicOr(flag, 8);
+  }
 }
 
 // Edge geometry in float64 from the fp32 inputs, then stored as fp32:
@@ -574,6 +702,10 @@ void launch_atom_struct(hipStream_t st, const int* offsets, int S, int N, int* s
 size_t scan_scratch_bytes(long long n) { return sizeof(long long) * (size_t)((n + kScanTile - 1) / kScanTile + 1); }
 
 void launch_exclusive_scan(hipStream_t st, const int* in, int n, int* out, int* flag, long long* scratch) {
+  if (n <= kScanOne) {
+    hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(kScanOneThreads), 0, st, in, n, out, flag);
+    return;
+  }
   const int ntiles = (int)cdiv(n, kScanTile);
   if (ntiles > 0) {
     hipLaunchKernelGGL(scan_tile_sums_kernel, dim3(ntiles), dim3(kScanThreads), 0, st, in, n, scratch);
@@ -647,15 +779,17 @@ extern "C" int janus_build_edges(janus_ctx* ctx, const float* pos, const float* 
   JANUS_HIP_TRY(hipStreamSynchronize(st));
   if (hw[0] & 1) return JANUS_EINVAL;
   if (hw[0] & 2) return JANUS_EUNSUPPORTED;
+  const bool cells = ctx->edge_builder == 1 || (ctx->edge_builder == 0 && (hw[0] & 32));
 
   const float r_cut = ctx->cfg.r_cut;
   const dim3 gw(cdiv((long long)N * 64, 256)), b256(256);
   {
     ProfScope ps(ctx, st, PROF_GRAPH, 0.0, 16.0 * N);
-    // cell lists of the structures that use them (none in mode 2)
-    hipLaunchKernelGGL(cell_grid_kernel, dim3(S), b256, 0, st, pos, cell, offsets, S, r_cut, ctx->edge_builder, grid,
-                       nbins);
-    if (ctx->edge_builder != 2) {
+    // cell lists of the structures that use them (none in mode 2, or without a large structure in mode 0)
+    if (!cells) grid = nullptr;
+    if (cells) {
+      hipLaunchKernelGGL(cell_grid_kernel, dim3(S), b256, 0, st, pos, cell, offsets, S, r_cut, ctx->edge_builder, grid,
+                         nbins);
       launch_exclusive_scan(st, nbins, S, bin_off, flag, scan);
       JANUS_HIP_TRY(hipMemsetAsync(bcount, 0, sizeof(int) * N, st));
       JANUS_HIP_TRY(hipMemsetAsync(bfill, 0, sizeof(int) * N, st));
@@ -664,10 +798,10 @@ extern "C" int janus_build_edges(janus_ctx* ctx, const float* pos, const float* 
       hipLaunchKernelGGL(cell_fill_kernel, dim3(cdiv(N, 256)), b256, 0, st, sid, grid, abin, bstart, N, bfill,
                          batoms);
       hipLaunchKernelGGL((nl_cell_kernel<false>), gw, b256, 0, st, pos, cell, offsets, sid, r_cut, N, grid, bin_off,
-                         bstart, batoms, count, nullptr, nullptr, nullptr, nullptr);
+                         bstart, batoms, count, nullptr, nullptr, nullptr, nullptr, nullptr);
     }
     hipLaunchKernelGGL((nl_kernel<false>), gw, b256, 0, st, pos, cell, offsets, sid, r_cut, N, count, nullptr,
-                       nullptr, nullptr, nullptr, grid);
+                       nullptr, nullptr, nullptr, nullptr, grid);
     launch_exclusive_scan(st, count, N, rp, flag, scan);
   }
   JANUS_HIP_TRY(hipGetLastError());
@@ -681,11 +815,11 @@ extern "C" int janus_build_edges(janus_ctx* ctx, const float* pos, const float* 
   JANUS_HIP_TRY(hipMemcpyAsync(rowptr, rp, sizeof(int) * (N + 1), hipMemcpyDeviceToDevice, st));
   if (ne > 0) {
     ProfScope ps(ctx, st, PROF_GRAPH, 0.0, 16.0 * N + 23.0 * ne);
-    if (ctx->edge_builder != 2)
+    if (cells)
       hipLaunchKernelGGL((nl_cell_kernel<true>), gw, b256, 0, st, pos, cell, offsets, sid, r_cut, N, grid, bin_off,
-                         bstart, batoms, count, rp, ei, ej, shift);
+                         bstart, batoms, count, rp, ei, ej, shift, rev);
     hipLaunchKernelGGL((nl_kernel<true>), gw, b256, 0, st, pos, cell, offsets, sid, r_cut, N, count, rp, ei, ej,
-                       shift, grid);
+                       shift, rev, grid);
     hipLaunchKernelGGL(reverse_kernel, dim3(cdiv(ne, 256)), dim3(256), 0, st, ei, ej, shift, rp, (int)ne, rev,
                        flag);
   }
