@@ -211,6 +211,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   // rounding (the step of 64 cells with 4 heads lies 2e-6 to 3e-3 from the 64-bit result,
   // depending on the batch, with either product), so its results are kept bit for bit.
   const bool split = !attn;
+  // From two column tiles of dW2 (d >= 256) the product before it stores g SiLU(A) for it (EpiP4):
+  // step of 32 mixed structures at d = 512 399 -> 377 ms.  With one tile SiLU is evaluated once anyway
+  // and the store only adds traffic (small batch with 4 heads 26.0 -> 26.5 ms).
+  const bool keep_s = split && d >= 256;
   const int H = p.H;
   // head width: the register-resident kernels (heads of 32 columns, neighbourhoods of
   // up to kAttnMfmaN edges) and the tiled sweeps beside them; wider heads take the
@@ -1053,8 +1057,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
-        launch_rows<true>(split, st, LoadPlain{p.T1f, d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
-                          EpiP4{Af(t), Sbf(t), SGF(t), hf}, p.gpartf);
+        if (keep_s)
+          launch_rows<true>(std::true_type{}, st, LoadPlain{p.T1f, d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
+                            EpiP4<true>{Af(t), Sbf(t), SGF(t), hf}, p.gpartf);
+        else
+          launch_rows<true>(split, st, LoadPlain{p.T1f, d}, W2f, d, hf, TLF(t), p.ntilesf + t, p.mtf,
+                            EpiP4<false>{Af(t), Sbf(t), SGF(t), hf}, p.gpartf);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_atm, 0);
@@ -1067,7 +1075,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_atm, 0);
-        launch_wgrad(split, st, LoadSiluRowScale{Af(t), SGF(t), hf}, LoadPlain{p.T1f, d}, hf, d, CHF(t), p.nchunksf + t, CFF(t),
+        if (keep_s)
+          launch_wgrad(split, st, LoadPlain{Af(t), hf}, LoadPlain{p.T1f, d}, hf, d, CHF(t), p.nchunksf + t, CFF(t),
+                     p.mcf, Ef, p.partial, Gp(blk(t, "W2f")), 1);
+        else
+          launch_wgrad(split, st, LoadSiluRowScale{Af(t), SGF(t), hf}, LoadPlain{p.T1f, d}, hf, d, CHF(t), p.nchunksf + t, CFF(t),
                      p.mcf, Ef, p.partial, Gp(blk(t, "W2f")), 1);
       }
       {
@@ -1188,8 +1200,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       // G9: St = mt W2^T -> At = g SiLU'(A) St + C (into Sb); row sums for the gate adjoint
       PROF(PROF_EXPERT_GEMM, f_exp, 0);
       // (with routing on the edge tokens the slot rows already carry the gates)
-      launch_rows<true>(split, st, LoadPlain{p.T1, d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
-                        EpiP4{Aa(t), Sb(t), p.rf ? (const float*)p.ones : SG(t), h}, p.gpart);
+      if (keep_s)
+        launch_rows<true>(std::true_type{}, st, LoadPlain{p.T1, d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
+                          EpiP4<true>{Aa(t), Sb(t), p.rf ? (const float*)p.ones : SG(t), h}, p.gpart);
+      else
+        launch_rows<true>(split, st, LoadPlain{p.T1, d}, W2, d, h, TL(t), p.ntiles + t, p.mt,
+                          EpiP4<false>{Aa(t), Sb(t), p.rf ? (const float*)p.ones : SG(t), h}, p.gpart);
     }
     {
       // G10: Xt = At W1^T
@@ -1200,7 +1216,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     {
       // G12: dW2 += SiLU(A)^T (g mt) (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
-      launch_wgrad(split, sd, LoadSiluRowScale{Aa(t), p.rf ? (const float*)p.ones : SG(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
+      if (keep_s)
+        launch_wgrad(split, sd, LoadPlain{Aa(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
+                   p.nchunks + t, CF(t), p.mc, Ee, p.partial2, Gp(blk(t, "W2")), 1);
+      else
+        launch_wgrad(split, sd, LoadSiluRowScale{Aa(t), p.rf ? (const float*)p.ones : SG(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
                    p.nchunks + t, CF(t), p.mc, Ee, p.partial2, Gp(blk(t, "W2")), 1);
     }
     t1_free = ss.mark();
@@ -1252,8 +1272,12 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ss.join();
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
-        launch_rows<true>(split, st, LoadPlain{p.T3a, d}, W2a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
-                          EpiP4{A3(t), S3b(t), SG3(t), h3}, p.gpart3);
+        if (keep_s)
+          launch_rows<true>(std::true_type{}, st, LoadPlain{p.T3a, d}, W2a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+                            EpiP4<true>{A3(t), S3b(t), SG3(t), h3}, p.gpart3);
+        else
+          launch_rows<true>(split, st, LoadPlain{p.T3a, d}, W2a, d, h3, TL3(t), p.ntiles3 + t, p.mt3,
+                            EpiP4<false>{A3(t), S3b(t), SG3(t), h3}, p.gpart3);
       }
       {
         PROF(PROF_EXPERT_GEMM, f_tri, 0);
@@ -1266,7 +1290,11 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       }
       {
         PROF(PROF_EXPERT_WGRAD, f_tri, 0);
-        launch_wgrad(split, st, LoadSiluRowScale{A3(t), SG3(t), h3}, LoadPlain{p.T3a, d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t),
+        if (keep_s)
+          launch_wgrad(split, st, LoadPlain{A3(t), h3}, LoadPlain{p.T3a, d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t),
+                     p.mc3, E3, p.partial, Gp(blk(t, "W2a")), 1);
+        else
+          launch_wgrad(split, st, LoadSiluRowScale{A3(t), SG3(t), h3}, LoadPlain{p.T3a, d}, h3, d, CH3(t), p.nchunks3 + t, CF3(t),
                      p.mc3, E3, p.partial, Gp(blk(t, "W2a")), 1);
       }
       {

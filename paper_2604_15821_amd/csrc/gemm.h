@@ -301,8 +301,11 @@ struct EpiP3 {
 
 // Final backward, after St = mt W2^T (ungated adjoint of the message):
 //   At = g SiLU'(A) St + C  (overwrites C); returns St . SiLU(A) for the gate adjoint.
+// KeepS: also g SiLU(A) over A (its last use), the operand of dW2, whose weight gradient else
+// evaluates SiLU and gate once per 128 output columns as it loads.
+template <bool KeepS>
 struct EpiP4 {
-  const float* A;
+  std::conditional_t<KeepS, float, const float>* A;
   float* Sb;
   const float* gate;
   long long ld;
@@ -311,9 +314,10 @@ struct EpiP4 {
     float4 a, c;
     float g;
   };
-  __device__ __forceinline__ static float one(float a, float v, float c, float g, float& sum) {
+  __device__ __forceinline__ static float one(float a, float v, float c, float g, float& sum, float& gs) {
     const float s = sig(a);
     sum += v * a * s;
+    gs = g * (a * s);
     return g * (s + a * s * (1.f - s)) * v + c;
   }
   __device__ __forceinline__ Raw load(long long r, int c) const {
@@ -322,12 +326,13 @@ struct EpiP4 {
   }
   __device__ __forceinline__ float store(long long r, int c, float4 v, const Raw& x) const {
     float sum = 0.f;
-    float4 o;
-    o.x = one(x.a.x, v.x, x.c.x, x.g, sum);
-    o.y = one(x.a.y, v.y, x.c.y, x.g, sum);
-    o.z = one(x.a.z, v.z, x.c.z, x.g, sum);
-    o.w = one(x.a.w, v.w, x.c.w, x.g, sum);
+    float4 o, gs;
+    o.x = one(x.a.x, v.x, x.c.x, x.g, sum, gs.x);
+    o.y = one(x.a.y, v.y, x.c.y, x.g, sum, gs.y);
+    o.z = one(x.a.z, v.z, x.c.z, x.g, sum, gs.z);
+    o.w = one(x.a.w, v.w, x.c.w, x.g, sum, gs.w);
     st4nt(Sb + r * ld + c, o);
+    if constexpr (KeepS) st4nt(A + r * ld + c, gs);
     return sum;
   }
 };
