@@ -254,8 +254,6 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       hipLaunchKernelGGL(tri_features_kernel, dim3(cdiv(Nt * (nf / 4), 256)), dim3(256), 0, st,
                          LoadTriFeat{p.te, p.te2, p.tc, p.B3, p.dB3, p.u3, p.du3, nullptr, nb}, Nt, nf, p.G3f);
     }
-    hipLaunchKernelGGL(set_rows_kernel, dim3(1), dim3(64), 0, st, p.rowT, (int)Nt, p.rowT, Nt);
-    build_tables(st, p.rowT, 1, p.kcT, p.tilesT, p.ntT, p.chunksT, p.ncT, p.cfT);
   }
   const long long np = (long long)nsp * nsp;
   {
@@ -263,13 +261,21 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     hipLaunchKernelGGL(species_count_kernel, dim3(nsp), dim3(64), 0, st, species, N, nsp, p.sp_cnt);
     launch_exclusive_scan(st, p.sp_cnt, nsp, p.sp_off, nullptr, p.scan);
     hipLaunchKernelGGL(species_write_kernel, dim3(nsp), dim3(64), 0, st, species, N, p.sp_off, p.sp_atoms);
-    hipLaunchKernelGGL(set_rows_kernel, dim3(1), dim3(64), 0, st, p.rowN, N, p.rowE, Ne);
-    build_tables(st, p.rowN, 1, p.kcN, p.tilesN, p.ntN, p.chunksN, p.ncN, p.cfN);
-    build_tables(st, p.rowE, 1, p.kcE, nullptr, nullptr, p.chunksE, p.ncE, p.cfE);
+    // tables of the products over all atoms, edges and triplets
+    TableJobs dense;
+    int n_dense = 0;
+    dense.job[n_dense++] = tables_of_rows(N).rows_tiles(p.tilesN, p.ntN).wgrad_chunks(p.kcN, p.chunksN, p.ncN, p.cfN);
+    dense.job[n_dense++] = tables_of_rows(Ne).wgrad_chunks(p.kcE, p.chunksE, p.ncE, p.cfE);
+    if (p.rf)
+      dense.job[n_dense++] = tables_of_rows(Ne).rows_tiles(p.tilesE, p.ntE).wgrad_chunks(p.kcR, p.chunksR, p.ncR, p.cfR);
+    if (attn)
+      dense.job[n_dense++] = tables_of_rows(Ne).rows_tiles(p.tilesE, p.ntE).wgrad_chunks(p.kcA, p.chunksA, p.ncA, p.cfA);
+    if (three)
+      dense.job[n_dense++] = tables_of_rows(Nt).rows_tiles(p.tilesT, p.ntT).wgrad_chunks(p.kcT, p.chunksT, p.ncT, p.cfT);
+    build_tables(st, dense, n_dense, 1);
     if (p.rf) {
-      // routing on the edge tokens: products over the edges, the identity slot map,
-      // gates of one, the zero-padded router weights and their gradient accumulators
-      build_tables(st, p.rowE, 1, p.kcR, p.tilesE, p.ntE, p.chunksR, p.ncR, p.cfR);
+      // routing on the edge tokens: the identity slot map, gates of one, the
+      // zero-padded router weights and their gradient accumulators
       hipLaunchKernelGGL(iota_kernel, dim3(cdiv(Ne + 1, 256)), dim3(256), 0, st, p.iotaE, (int)Ne);
       hipLaunchKernelGGL(fill_kernel, dim3(cdiv(M + 1, 256)), dim3(256), 0, st, p.ones, M + 1, 1.f);
       for (int t = 0; t < T; ++t)
@@ -277,17 +283,19 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
                            Wp(blk(t, "Wr")), d, Ee, p.Ep, p.WrP + (long long)t * d * p.Ep);
       JANUS_HIP_TRY(hipMemsetAsync(p.dWrP, 0, sizeof(float) * T * d * p.Ep, st));
     }
-    if (attn) {
-      build_tables(st, p.rowE, 1, p.kcA, p.tilesE, p.ntE, p.chunksA, p.ncA, p.cfA);
-      if (Ne > 0)
-        hipLaunchKernelGGL(attn_env_kernel, dim3(cdiv(Ne, 256)), dim3(256), 0, st, (const float4*)p.geo, Ne,
-                           cfg.r_cut, p.eu, p.eud);
-    }
-    for (int t = 0; t < T; ++t) {
+    if (attn && Ne > 0)
+      hipLaunchKernelGGL(attn_env_kernel, dim3(cdiv(Ne, 256)), dim3(256), 0, st, (const float4*)p.geo, Ne, cfg.r_cut,
+                         p.eu, p.eud);
+    // every block's routing depends on the species only, so all blocks share the launches (a
+    // launch takes 2 to 5 us however little it does)
+    const long long wstride = T > 1 ? L.at(blk(1, "Pc")) - L.at(blk(0, "Pc")) : 0;
+    if (T > 0 && !p.rf) {   // routing on the edge tokens is decided in the forward pass
       RouteArgs ra;
-      ra.Pc = Wp(blk(t, "Pc"));
-      ra.Pn = Wp(blk(t, "Pn"));
-      ra.beta = Wp(blk(t, "beta"));
+      ra.T = T;
+      ra.wstride = wstride;
+      ra.Pc = Wp(blk(0, "Pc"));
+      ra.Pn = Wp(blk(0, "Pn"));
+      ra.beta = Wp(blk(0, "beta"));
       ra.species = species;
       ra.ei = ei;
       ra.ej = ej;
@@ -295,60 +303,59 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
       ra.nsp = nsp;
       ra.E = Ee;
       ra.k = k;
-      ra.peid = p.peid + t * np * k;
-      ra.pgate = p.pgate + t * np * k;
-      ra.pprob = p.pprob + t * np * Ee;
-      ra.pair = p.pair + t * Ne;
-      ra.eid = p.eid + t * M;
-      ra.gate = p.gate + t * M;
+      ra.peid = p.peid;
+      ra.pgate = p.pgate;
+      ra.pprob = p.pprob;
+      ra.pair = p.pair;
+      ra.eid = p.eid;
+      ra.gate = p.gate;
       ra.cnt = p.cnt;
       ra.colpre = p.colpre;
-      ra.total = p.total + t * Ee;
-      ra.off = p.off + t * (Ee + 1);
-      ra.pos = p.pos + t * M;
-      ra.slot_gate = p.slot_gate + t * M;
-      if (!p.rf) {   // routing on the edge tokens is decided in the forward pass
-        route_block(st, ra);
-        build_tables(st, ra.off, Ee, p.kc, p.tiles + (long long)t * p.mt, p.ntiles + t,
-                     p.chunks + (long long)t * p.mc, p.nchunks + t, p.cfirst + t * (Ee + 1));
-      }
-      if (three) {
-        if (Nt > 0)
+      ra.total = p.total;
+      ra.off = p.off;
+      ra.pos = p.pos;
+      ra.slot_gate = p.slot_gate;
+      route_blocks(st, ra, tables_from_totals(p.total, p.off, Ee).rows_tiles(p.tiles, p.ntiles, p.mt)
+                               .wgrad_chunks(p.kc, p.chunks, p.nchunks, p.cfirst, p.mc));
+    }
+    if (T > 0 && three) {
+      if (Nt > 0)
+        for (int t = 0; t < T; ++t)
           hipLaunchKernelGGL(tri_route_kernel, dim3(cdiv(Nt, 128)), dim3(128), 0, st, species, ei, ej,
                              (const int*)p.te, (const int*)p.te2, Nt, Wp(blk(t, "P3a")), Wp(blk(t, "P3b")),
                              Wp(blk(t, "P3c")), Wp(blk(t, "beta3")), E3, k3, p.eid3 + t * M3, p.gate3 + t * M3);
-        sort_tokens(st, p.eid3 + t * M3, p.gate3 + t * M3, M3, E3, p.cnt3, p.colpre3, p.total3 + t * E3,
-                    p.off3 + t * (E3 + 1), p.pos3 + t * M3, p.slot_gate3 + t * M3);
-        if (Nt > 0)
+      sort_tokens(st, p.eid3, p.gate3, M3, E3, p.cnt3, p.colpre3, p.total3, p.off3, p.pos3, p.slot_gate3,
+                  tables_from_totals(p.total3, p.off3, E3).rows_tiles(p.tiles3, p.ntiles3, p.mt3)
+                      .wgrad_chunks(p.kc3, p.chunks3, p.nchunks3, p.cfirst3, p.mc3), T);
+      if (Nt > 0)
+        for (int t = 0; t < T; ++t)
           hipLaunchKernelGGL(tri_pos_rev_kernel, dim3(cdiv(Nt, 256)), dim3(256), 0, st, (const int*)p.trev,
                              (const int*)(p.pos3 + t * M3), Nt, k3, p.pos3r + t * M3);
-        build_tables(st, p.off3 + t * (E3 + 1), E3, p.kc3, p.tiles3 + (long long)t * p.mt3, p.ntiles3 + t,
-                     p.chunks3 + (long long)t * p.mc3, p.nchunks3 + t, p.cfirst3 + t * (E3 + 1));
-      }
-      if (atom) {
-        AtomRouteArgs fa;
-        fa.Pf = Wp(blk(t, "Pf"));
-        fa.beta = Wp(blk(t, "betaf"));
-        fa.species = species;
-        fa.N = N;
-        fa.nsp = nsp;
-        fa.E = Ef;
-        fa.k = kf;
-        fa.seid = p.seid + (long long)t * nsp * kf;
-        fa.sgate = p.sgate + (long long)t * nsp * kf;
-        fa.sprob = p.sprob + (long long)t * nsp * Ef;
-        fa.eid = p.eidf + t * Mf;
-        fa.gate = p.gatef + t * Mf;
-        fa.cnt = p.cntf;
-        fa.colpre = p.colpref;
-        fa.total = p.totalf + t * Ef;
-        fa.off = p.offf + t * (Ef + 1);
-        fa.pos = p.posf + t * Mf;
-        fa.slot_gate = p.slot_gatef + t * Mf;
-        route_atoms(st, fa);
-        build_tables(st, fa.off, Ef, p.kcf, p.tilesf + (long long)t * p.mtf, p.ntilesf + t,
-                     p.chunksf + (long long)t * p.mcf, p.nchunksf + t, p.cfirstf + t * (Ef + 1));
-      }
+    }
+    if (T > 0 && atom) {
+      AtomRouteArgs fa;
+      fa.T = T;
+      fa.wstride = wstride;
+      fa.Pf = Wp(blk(0, "Pf"));
+      fa.beta = Wp(blk(0, "betaf"));
+      fa.species = species;
+      fa.N = N;
+      fa.nsp = nsp;
+      fa.E = Ef;
+      fa.k = kf;
+      fa.seid = p.seid;
+      fa.sgate = p.sgate;
+      fa.sprob = p.sprob;
+      fa.eid = p.eidf;
+      fa.gate = p.gatef;
+      fa.cnt = p.cntf;
+      fa.colpre = p.colpref;
+      fa.total = p.totalf;
+      fa.off = p.offf;
+      fa.pos = p.posf;
+      fa.slot_gate = p.slot_gatef;
+      route_atoms(st, fa, tables_from_totals(p.totalf, p.offf, Ef).rows_tiles(p.tilesf, p.ntilesf, p.mtf)
+                              .wgrad_chunks(p.kcf, p.chunksf, p.nchunksf, p.cfirstf, p.mcf));
     }
   }
   JANUS_HIP_TRY(hipGetLastError());
@@ -494,9 +501,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
                              Wp(blk(t, "Pc")), Wp(blk(t, "Pn")), Wp(blk(t, "beta")), Ne, Ee, (int)Ep, k,
                              p.eid + t * M, p.gate + t * M, FPR(t), gap);
         sort_tokens(st, p.eid + t * M, p.gate + t * M, M, Ee, p.cnt, p.colpre, p.total + t * Ee, p.off + t * (Ee + 1),
-                    p.pos + t * M, p.slot_gate + t * M);
-        build_tables(st, p.off + t * (Ee + 1), Ee, p.kc, p.tiles + (long long)t * p.mt, p.ntiles + t,
-                     p.chunks + (long long)t * p.mc, p.nchunks + t, p.cfirst + t * (Ee + 1));
+                    p.pos + t * M, p.slot_gate + t * M,
+                    tables_from_totals(p.total + t * Ee, p.off + t * (Ee + 1), Ee)
+                        .rows_tiles(p.tiles + (long long)t * p.mt, p.ntiles + t)
+                        .wgrad_chunks(p.kc, p.chunks + (long long)t * p.mc, p.nchunks + t, p.cfirst + t * (Ee + 1)), 1);
       }
       if (Ne > 0) {
         PROF(PROF_EDGE, 0, Ne * (4.0 * d + 8.0 * k + 4.0 * k * d));
@@ -1096,7 +1104,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
                            (const float*)(p.sprob + (long long)t * nsp * Ef), (const int*)(p.eidf + t * Mf),
                            (const float*)p.gtf, (long long)N, kf, Ef, p.ltf);
         hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.ltf, Ef, nsp, Gp(blk(t, "Pf")));
+                           (const int*)p.sp_atoms, SpeciesRows{{p.ltf}, {Gp(blk(t, "Pf"))}}, Ef, nsp);
       }
       a_u = p.ut;
     }
@@ -1214,7 +1222,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     }
     ss.fork();
     {
-      // G12: dW2 += SiLU(A)^T (g mt) (side stream)
+      // G12: dW2 += (g SiLU(A))^T mt (side stream)
       PROFS(sd, PROF_EXPERT_WGRAD, f_exp, 0);
       if (keep_s)
         launch_wgrad(split, sd, LoadPlain{Aa(t), h}, LoadPlain{p.T1, d}, h, d, CH(t),
@@ -1254,10 +1262,9 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
         }
         hipLaunchKernelGGL(router_atom_kernel, gN, b256, 0, st, rowptr, rev, Ee,
                            (const float*)p.lte, N, p.partC, p.partN);
-        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.partC, Ee, nsp, Gp(blk(t, "Pc")));
-        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.partN, Ee, nsp, Gp(blk(t, "Pn")));
+        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp, 2), b256, 0, st, (const int*)p.sp_off,
+                           (const int*)p.sp_atoms,
+                           SpeciesRows{{p.partC, p.partN}, {Gp(blk(t, "Pc")), Gp(blk(t, "Pn"))}}, Ee, nsp);
       }
     }
     if (three && Nt > 0) {
@@ -1325,12 +1332,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
                            (const int*)p.trev, E3, (const float*)p.LT3, Ne, p.LB, p.LC);
         hipLaunchKernelGGL(tri_router_atom_kernel, gN, b256, 0, st, rowptr, rev, E3, (const float*)p.LB,
                            (const float*)p.LC, N, p.pa, p.pb, p.pc);
-        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.pa, E3, nsp, Gp(blk(t, "P3a")));
-        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.pb, E3, nsp, Gp(blk(t, "P3b")));
-        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                           (const int*)p.sp_atoms, (const float*)p.pc, E3, nsp, Gp(blk(t, "P3c")));
+        hipLaunchKernelGGL(species_rows_kernel, dim3(nsp, 3), b256, 0, st, (const int*)p.sp_off,
+                           (const int*)p.sp_atoms,
+                           SpeciesRows{{p.pa, p.pb, p.pc},
+                                       {Gp(blk(t, "P3a")), Gp(blk(t, "P3b")), Gp(blk(t, "P3c"))}}, E3, nsp);
       }
     }
     {
@@ -1365,7 +1370,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   {
     PROF(PROF_OTHER, 0, 8.0 * Nd);
     hipLaunchKernelGGL(species_rows_kernel, dim3(nsp), b256, 0, st, (const int*)p.sp_off,
-                       (const int*)p.sp_atoms, (const float*)HV(p.hh, 0), d, nsp, Gp("A"));
+                       (const int*)p.sp_atoms, SpeciesRows{{HV(p.hh, 0)}, {Gp("A")}}, d, nsp);
     if (cfg.n_tasks) {
       // per-structure sums of dL/dh0, then per label value and per species (composition)
       LAUNCH_VPL(struct_sum_kernel, d, wave_grid(S), b256, 0, st, offsets, (const float*)HV(p.hh, 0), S, d, p.gsb);

@@ -12,9 +12,10 @@
 //
 //  * gemm_wgrad: G_g[p, q] = sum_{r in group g} A[r, p] B[r, q], the weight
 //    gradients, whose contraction runs over the tokens of an expert.  The
-//    rows of each group are cut into chunks; each chunk writes a partial
-//    P x Q block and a second kernel adds the chunks of a group in order,
-//    so the result does not depend on scheduling.
+//    rows of each group are cut into chunks; a group's only chunk writes the
+//    gradient itself, else each chunk writes a partial P x Q block and a second
+//    kernel adds the chunks of a group in order, so the result does not depend
+//    on scheduling.
 //
 // Work decomposition: a workgroup of 256 threads (4 waves as 2 x 2) owns a
 // 128 x 128 output tile; each wave owns 64 x 64 = 2 x 2 MFMA blocks of
@@ -956,7 +957,7 @@ struct WChunk {
   int group;
   int r0;
   int r1;
-  int pad;
+  int alone;        // 1: the group's only chunk
 };
 
 // The contraction on the fp32 matrix instructions.
@@ -1028,7 +1029,8 @@ __device__ __forceinline__ bool wgrad_split(float* smem, const ALoad& al, const 
 template <class ALoad, class BLoad, bool Split>
 __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
                                                  const WChunk* __restrict__ chunks,
-                                                 const int* __restrict__ n_chunks, float* __restrict__ partial) {
+                                                 const int* __restrict__ n_chunks, float* __restrict__ partial,
+                                                 float* __restrict__ G, int accumulate) {
   const int ntq = (Q + GBN - 1) / GBN;
   int c, pq;
   xcd_map(vb, ((P + GBM - 1) / GBM) * ntq, c, pq);
@@ -1051,34 +1053,50 @@ __device__ __forceinline__ void gemm_wgrad_block(int vb, float* smem, const ALoa
     wgrad_fp32(smem, al, bl, P, Q, ch, p0, q0, wm, wn, lr, hf, tid, acc);
   }
 
-  float* out = partial + (long long)c * P * Q;
+  // the only chunk of a group writes (adds to) its gradient, one of several writes a partial block
+  auto put = [&](float* out, auto add) {
+    constexpr bool Add = decltype(add)::value;
 #pragma unroll
-  for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
-      const int pr = p0 + wm * 64 + (paired ? 2 * i + bi : bi * 32 + i);
-      if (paired) {
-        const int qc = q0 + wn * 64 + 2 * lr;
-        if (pr < P && qc < Q)
-          *reinterpret_cast<float2*>(out + (long long)pr * Q + qc) = make_float2(acc[bi][0][v], acc[bi][1][v]);
-      } else {
+      for (int v = 0; v < 16; ++v) {
+        const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
+        const int pr = p0 + wm * 64 + (paired ? 2 * i + bi : bi * 32 + i);
+        if (paired) {
+          const int qc = q0 + wn * 64 + 2 * lr;
+          if (pr < P && qc < Q) {
+            float2* o = reinterpret_cast<float2*>(out + (long long)pr * Q + qc);
+            float2 x = make_float2(acc[bi][0][v], acc[bi][1][v]);
+            if (Add) x = make_float2(o->x + x.x, o->y + x.y);
+            *o = x;
+          }
+        } else {
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-          const int qc = q0 + wn * 64 + bj * 32 + lr;
-          if (pr < P && qc < Q) out[(long long)pr * Q + qc] = acc[bi][bj][v];
+          for (int bj = 0; bj < 2; ++bj) {
+            const int qc = q0 + wn * 64 + bj * 32 + lr;
+            float* o = out + (long long)pr * Q + qc;
+            if (pr < P && qc < Q) *o = Add ? *o + acc[bi][bj][v] : acc[bi][bj][v];
+          }
         }
       }
-    }
+  };
+  if (!ch.alone)
+    put(partial + (long long)c * P * Q, std::false_type{});
+  else if (accumulate)
+    put(G + (long long)ch.group * P * Q, std::true_type{});
+  else
+    put(G + (long long)ch.group * P * Q, std::false_type{});
 }
 
 template <class ALoad, class BLoad, bool Split>
 __global__ __launch_bounds__(256, 2) void gemm_wgrad_kernel(ALoad al, BLoad bl, int P, int Q,
                                                             const WChunk* __restrict__ chunks,
                                                             const int* __restrict__ n_chunks,
-                                                            float* __restrict__ partial) {
+                                                            float* __restrict__ partial, float* __restrict__ G,
+                                                            int accumulate) {
   __shared__ __attribute__((aligned(16))) float smem[Split ? SMEM_FLOATS : SMEM_FP32];
-  gemm_wgrad_block<ALoad, BLoad, Split>(blockIdx.x, smem, al, bl, P, Q, chunks, n_chunks, partial);
+  gemm_wgrad_block<ALoad, BLoad, Split>(blockIdx.x, smem, al, bl, P, Q, chunks, n_chunks, partial, G,
+                                        accumulate);
 }
 
 // ---------------------------------------------------------- skinny wgrad

@@ -6,65 +6,67 @@
 
 namespace janus {
 
-__global__ void build_rows_tiles_kernel(const int* __restrict__ row_off, int n_groups, RowsTile* tiles,
-                                        int* n_tiles) {
-  __shared__ int pre[1025];
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int g = 0; g < n_groups; ++g) {
-      pre[g] = acc;
-      int m = row_off[g + 1] - row_off[g];
-      acc += (m + GBM - 1) / GBM;
+// Tables of one or several grouped products: workgroup x builds job x's, for block y of the job's
+// strides.  Group sizes come from the row offsets, from token totals (the offsets are then
+// written too) or, with neither, from one group of `rows` rows.  Every launch of this kernel takes 2 to
+// 3 us whatever it builds, so all tables that are ready together share one.
+__global__ __launch_bounds__(256) void build_tables_kernel(TableJobs jobs) {
+  __shared__ int off[1025], tpre[1025], cpre[1025];
+  const TableJob j = jobs.job[blockIdx.x];
+  const long long y = blockIdx.y;
+  const int n = j.groups;
+  if (j.totals) {
+    if ((int)threadIdx.x < n) tpre[threadIdx.x] = j.totals[y * n + threadIdx.x];   // at most 64 experts
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int acc = 0;
+      for (int g = 0; g < n; ++g) {
+        off[g] = acc;
+        acc += tpre[g];
+      }
+      off[n] = acc;
     }
-    pre[n_groups] = acc;
-    *n_tiles = acc;
+    __syncthreads();
+    if ((int)threadIdx.x <= n) j.off_out[y * (n + 1) + threadIdx.x] = off[threadIdx.x];
+  } else {
+    for (int g = threadIdx.x; g <= n; g += blockDim.x) off[g] = j.off ? j.off[y * (n + 1) + g] : g ? j.rows : 0;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    int t = 0, c = 0;
+    for (int g = 0; g < n; ++g) {
+      const int m = off[g + 1] - off[g];
+      tpre[g] = t;
+      cpre[g] = c;
+      t += (m + GBM - 1) / GBM;
+      if (j.chunks) c += (m + j.kc - 1) / j.kc;
+    }
+    tpre[n] = t;
+    cpre[n] = c;
   }
   __syncthreads();
-  const int total = pre[n_groups];
-  for (int t = threadIdx.x; t < total; t += blockDim.x) {
-    int lo = 0, hi = n_groups;   // pre[lo] <= t < pre[hi]
+  auto find = [&](const int* pre, int q) {   // the group g with pre[g] <= q < pre[g + 1]
+    int lo = 0, hi = n;
     while (hi - lo > 1) {
-      int mid = (lo + hi) >> 1;
-      if (pre[mid] <= t) lo = mid; else hi = mid;
+      const int mid = (lo + hi) >> 1;
+      if (pre[mid] <= q) lo = mid; else hi = mid;
     }
-    RowsTile e;
-    e.group = lo;
-    e.r0 = row_off[lo] + (t - pre[lo]) * GBM;
-    e.r1 = row_off[lo + 1];
-    e.pad = 0;
-    tiles[t] = e;
+    return lo;
+  };
+  if (j.tiles) {
+    if (threadIdx.x == 0) j.n_tiles[y] = tpre[n];
+    for (int q = threadIdx.x; q < tpre[n]; q += blockDim.x) {
+      const int g = find(tpre, q);
+      j.tiles[y * j.tile_stride + q] = RowsTile{g, off[g] + (q - tpre[g]) * GBM, off[g + 1], 0};
+    }
   }
-}
-
-__global__ void build_wchunks_kernel(const int* __restrict__ row_off, int n_groups, int kc, WChunk* chunks,
-                                     int* n_chunks, int* chunk_first) {
-  __shared__ int pre[1025];
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int g = 0; g < n_groups; ++g) {
-      pre[g] = acc;
-      chunk_first[g] = acc;
-      int m = row_off[g + 1] - row_off[g];
-      acc += (m + kc - 1) / kc;
+  if (j.chunks) {
+    if (threadIdx.x == 0) j.n_chunks[y] = cpre[n];
+    for (int g = threadIdx.x; g <= n; g += blockDim.x) j.chunk_first[y * (n + 1) + g] = cpre[g];
+    for (int q = threadIdx.x; q < cpre[n]; q += blockDim.x) {
+      const int g = find(cpre, q), r0 = off[g] + (q - cpre[g]) * j.kc;
+      j.chunks[y * j.chunk_stride + q] = WChunk{g, r0, min(r0 + j.kc, off[g + 1]), cpre[g + 1] - cpre[g] == 1};
     }
-    pre[n_groups] = acc;
-    chunk_first[n_groups] = acc;
-    *n_chunks = acc;
-  }
-  __syncthreads();
-  const int total = pre[n_groups];
-  for (int t = threadIdx.x; t < total; t += blockDim.x) {
-    int lo = 0, hi = n_groups;
-    while (hi - lo > 1) {
-      int mid = (lo + hi) >> 1;
-      if (pre[mid] <= t) lo = mid; else hi = mid;
-    }
-    WChunk e;
-    e.group = lo;
-    e.r0 = row_off[lo] + (t - pre[lo]) * kc;
-    e.r1 = min(e.r0 + kc, row_off[lo + 1]);
-    e.pad = 0;
-    chunks[t] = e;
   }
 }
 
@@ -74,13 +76,15 @@ __global__ void build_wchunks_kernel(const int* __restrict__ row_off, int n_grou
 // result is the same on every run.
 constexpr int kRedSlices = 16;
 __global__ void wgrad_reduce_kernel(const float* __restrict__ partial, const int* __restrict__ chunk_first,
-                                    int n_groups, long long PQ, float* __restrict__ G, int accumulate) {
+                                    int n_groups, long long PQ, float* __restrict__ G, int accumulate,
+                                    bool alone_done) {
   __shared__ float4 red[kRedSlices][16];
   const int g = blockIdx.y;
   const int cl = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const long long i4 = (long long)blockIdx.x * 16 + cl;
   const bool ok = 4 * i4 < PQ;
   const int c0 = chunk_first[g], c1 = chunk_first[g + 1];
+  if (alone_done && (c1 - c0 == 1 || (c1 == c0 && accumulate))) return;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
   if (ok) {
     int c = c0 + sl;
@@ -123,19 +127,14 @@ int skinny_chunk_rows(long long M, int P, int Q) {
 }
 
 void launch_wgrad_reduce(hipStream_t st, const float* partial, const int* chunk_first, int groups,
-                         long long PQ, float* G, int accumulate) {
+                         long long PQ, float* G, int accumulate, bool alone_done) {
   dim3 rg(cdiv(PQ / 4, 16), groups);
   hipLaunchKernelGGL(wgrad_reduce_kernel, rg, dim3(16 * kRedSlices), 0, st, partial, chunk_first, groups, PQ, G,
-                     accumulate);
+                     accumulate, alone_done);
 }
 
-// Tile and chunk tables from group row offsets (one workgroup).
-void build_tables(hipStream_t st, const int* row_off, int groups, int kc, RowsTile* tiles, int* n_tiles,
-                  WChunk* chunks, int* n_chunks, int* chunk_first) {
-  if (tiles) hipLaunchKernelGGL(build_rows_tiles_kernel, dim3(1), dim3(256), 0, st, row_off, groups, tiles, n_tiles);
-  if (chunks)
-    hipLaunchKernelGGL(build_wchunks_kernel, dim3(1), dim3(256), 0, st, row_off, groups, kc, chunks, n_chunks,
-                       chunk_first);
+void build_tables(hipStream_t st, const TableJobs& jobs, int n_jobs, int n_blocks) {
+  hipLaunchKernelGGL(build_tables_kernel, dim3(n_jobs, n_blocks), dim3(256), 0, st, jobs);
 }
 
 int ensure(janus_buffer& b, size_t bytes) {
@@ -176,7 +175,7 @@ extern "C" int janus_grouped_gemm(janus_ctx* ctx, const float* A, const float* B
   Carver c2(ctx->aux.ptr);
   RowsTile* tiles = c2.take<RowsTile>(mt);
   int* nt = c2.take<int>(1);
-  build_tables(st, row_off, n_groups, 0, tiles, nt, nullptr, nullptr, nullptr);
+  build_tables(st, tables_of(row_off, n_groups).rows_tiles(tiles, nt));
   if (trans_b)
     launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   else
@@ -239,7 +238,7 @@ extern "C" int janus_grouped_gemm_noalloc(const float* A, const float* B, float*
   if (cv.size() > kNoAllocScratchBytes) return JANUS_ENOMEM;
   // the table kernel rewrites the count and every tile the launch reads, so
   // nothing left by an earlier call is used
-  build_tables(st, row_off, n_groups, 0, tiles, nt, nullptr, nullptr, nullptr);
+  build_tables(st, tables_of(row_off, n_groups).rows_tiles(tiles, nt));
   if (trans_b)
     launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
   else
@@ -274,7 +273,7 @@ extern "C" int janus_grouped_wgrad(janus_ctx* ctx, const float* A, const float* 
   int* nc = c2.take<int>(1);
   int* first = c2.take<int>(n_groups + 1);
   float* partial = c2.take<float>((size_t)mc * P * Q);
-  build_tables(st, row_off, n_groups, kc, nullptr, nullptr, chunks, nc, first);
+  build_tables(st, tables_of(row_off, n_groups).wgrad_chunks(kc, chunks, nc, first));
   launch_wgrad(std::true_type{}, st, LoadPlain{A, P}, LoadPlain{B, Q}, P, Q, chunks, nc, first, mc, n_groups, partial, G, 0);
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;

@@ -151,8 +151,9 @@ inline const void* skinny_kernel(int P, int Q) {
 #undef JANUS_SKINNY_CW
 }
 
+// alone_done: groups of one chunk have their gradient already (gemm_wgrad).
 void launch_wgrad_reduce(hipStream_t st, const float* partial, const int* chunk_first, int groups,
-                         long long PQ, float* G, int accumulate);
+                         long long PQ, float* G, int accumulate, bool alone_done);
 
 // Launch helpers (the tables must have been built on `st` beforehand).  `split` selects the
 // split products (true) or the fp32 matrix instructions (false); kFp32 says false at compile
@@ -196,15 +197,18 @@ void launch_wgrad(S split, hipStream_t st, const ALoad& al, const BLoad& bl, int
     if constexpr (!std::is_same_v<S, Fp32Only>) {
       if (split && split_takes_wgrad(P, Q)) {
         hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad, true>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
-                           n_chunks, partial);
+                           n_chunks, partial, G, accumulate);
         launched = true;
       }
     }
     if (!launched)
       hipLaunchKernelGGL((gemm_wgrad_kernel<ALoad, BLoad, false>), grid, dim3(256), 0, st, al, bl, P, Q, chunks,
-                         n_chunks, partial);
+                         n_chunks, partial, G, accumulate);
   }
-  launch_wgrad_reduce(st, partial, chunk_first, groups, (long long)P * Q, G, accumulate);
+  // with at most one chunk per group (max_chunks counts ceil(M / chunk) + groups) the products
+  // have added everything
+  if (accumulate && max_chunks <= groups + 1) return;
+  launch_wgrad_reduce(st, partial, chunk_first, groups, (long long)P * Q, G, accumulate, true);
 }
 
 // Skinny weight gradient (P <= 32, Q <= 512, P and Q multiples of 4, one group):
@@ -217,10 +221,65 @@ inline void launch_wgrad_skinny(hipStream_t st, const float* A, const float* s, 
                     (void*)&partial};
     (void)hipLaunchKernel(skinny_kernel(P, Q), dim3(max_chunks), dim3(256), args, sizeof(float) * P * Q, st);
   }
-  launch_wgrad_reduce(st, partial, chunk_first, 1, (long long)P * Q, G, accumulate);
+  launch_wgrad_reduce(st, partial, chunk_first, 1, (long long)P * Q, G, accumulate, false);
 }
 
-void build_tables(hipStream_t st, const int* row_off, int groups, int kc, RowsTile* tiles, int* n_tiles,
-                  WChunk* chunks, int* n_chunks, int* chunk_first);
+// One product's tile and chunk tables (either may be left out); strides between blocks of a launch:
+// groups for totals, groups + 1 for offsets and chunk_first, 1 for the counts, and as given below.
+struct TableJob {
+  const int* off = nullptr;      // row offsets of the groups,
+  const int* totals = nullptr;   // or rows per group (at most 64 groups; offsets go to off_out),
+  int* off_out = nullptr;
+  int rows = 0;                  // or one group of this many rows
+  int groups = 1;
+  RowsTile* tiles = nullptr;
+  int* n_tiles = nullptr;
+  long long tile_stride = 0;
+  int kc = 0;
+  WChunk* chunks = nullptr;
+  int *n_chunks = nullptr, *chunk_first = nullptr;
+  long long chunk_stride = 0;
+  TableJob& rows_tiles(RowsTile* t, int* n, long long stride = 0) {
+    tiles = t;
+    n_tiles = n;
+    tile_stride = stride;
+    return *this;
+  }
+  TableJob& wgrad_chunks(int chunk, WChunk* c, int* n, int* first, long long stride = 0) {
+    kc = chunk;
+    chunks = c;
+    n_chunks = n;
+    chunk_first = first;
+    chunk_stride = stride;
+    return *this;
+  }
+};
+struct TableJobs {
+  TableJob job[6];
+};
+inline TableJob tables_of(const int* off, int groups) {
+  TableJob j;
+  j.off = off;
+  j.groups = groups;
+  return j;
+}
+inline TableJob tables_of_rows(long long rows) {
+  TableJob j;
+  j.rows = (int)rows;
+  return j;
+}
+inline TableJob tables_from_totals(const int* totals, int* off_out, int groups) {
+  TableJob j;
+  j.totals = totals;
+  j.off_out = off_out;
+  j.groups = groups;
+  return j;
+}
+void build_tables(hipStream_t st, const TableJobs& jobs, int n_jobs, int n_blocks);
+inline void build_tables(hipStream_t st, const TableJob& job, int n_blocks = 1) {
+  TableJobs jobs;
+  jobs.job[0] = job;
+  build_tables(st, jobs, 1, n_blocks);
+}
 
 }  // namespace janus

@@ -2,10 +2,15 @@
 #pragma once
 
 #include "common.h"
+#include "internal.h"
 
 namespace janus {
 
+// All T blocks at once: block t's weights lie t * wstride after block 0's, every other array holds the
+// T blocks one after the other in the shapes given here.
 struct RouteArgs {
+  int T;
+  long long wstride;
   const float* Pc;        // [nsp, E]
   const float* Pn;        // [nsp, E]
   const float* beta;      // [E]
@@ -29,6 +34,8 @@ struct RouteArgs {
 
 // Routing of the atom tokens of the feature-update MoE (logits Pf[Z_i] + beta).
 struct AtomRouteArgs {
+  int T;
+  long long wstride;
   const float* Pf;        // [nsp, E]
   const float* beta;      // [E]
   const int* species;     // [N]
@@ -47,13 +54,14 @@ struct AtomRouteArgs {
 };
 
 __global__ void zero_ints_kernel(int* p, int n);
-void route_atoms(hipStream_t st, const AtomRouteArgs& a);
-void route_block(hipStream_t st, const RouteArgs& a);
+void route_atoms(hipStream_t st, const AtomRouteArgs& a, const TableJob& tables);
+void route_blocks(hipStream_t st, const RouteArgs& a, const TableJob& tables);
 // Stable counting sort of M tokens (flattened (token, choice) entries with
 // expert ids eid) into expert-grouped slots: total[E], off[E+1], pos[M],
-// slot_gate[M]; cnt and colpre are scratch of sort_chunks(M) * E ints.
+// slot_gate[M], and the product tables of `tables` (from total, into off); cnt and colpre are scratch
+// of sort_chunks(M) * E ints.  T blocks at once, one after the other in every array.
 void sort_tokens(hipStream_t st, const int* eid, const float* gate, long long M, int E, int* cnt, int* colpre,
-                 int* total, int* off, int* pos, float* slot_gate);
+                 int* total, int* off, int* pos, float* slot_gate, const TableJob& tables, int T);
 int sort_chunks(long long M);
 
 }  // namespace janus

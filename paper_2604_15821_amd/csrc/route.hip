@@ -52,9 +52,17 @@ __device__ void topk_softmax(L32 l32, L64 l64, int E, int k, int* __restrict__ e
 // One thread per species pair p = a * n_species + b.
 __global__ void route_pairs_kernel(const float* __restrict__ Pc, const float* __restrict__ Pn,
                                    const float* __restrict__ beta, int nsp, int E, int k,
-                                   int* __restrict__ peid, float* __restrict__ pgate, float* __restrict__ pprob) {
+                                   int* __restrict__ peid, float* __restrict__ pgate, float* __restrict__ pprob,
+                                   long long wstride) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= nsp * nsp) return;
+  const long long t = blockIdx.y, np = (long long)nsp * nsp;
+  Pc += t * wstride;
+  Pn += t * wstride;
+  beta += t * wstride;
+  peid += t * np * k;
+  pgate += t * np * k;
+  pprob += t * np * E;
   const float* pa = Pc + (long long)(p / nsp) * E;
   const float* pb = Pn + (long long)(p % nsp) * E;
   topk_softmax([&](int x) { return __fadd_rn(__fadd_rn(pa[x], pb[x]), beta[x]); },
@@ -65,9 +73,15 @@ __global__ void route_pairs_kernel(const float* __restrict__ Pc, const float* __
 // Feature-update MoE, one thread per species a: logits Pf[a] + betaf.
 __global__ void route_species_kernel(const float* __restrict__ Pf, const float* __restrict__ beta, int nsp, int E,
                                      int k, int* __restrict__ seid, float* __restrict__ sgate,
-                                     float* __restrict__ sprob) {
+                                     float* __restrict__ sprob, long long wstride) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nsp) return;
+  const long long t = blockIdx.y;
+  Pf += t * wstride;
+  beta += t * wstride;
+  seid += t * nsp * k;
+  sgate += t * nsp * k;
+  sprob += t * nsp * E;
   const float* pa = Pf + (long long)a * E;
   topk_softmax([&](int x) { return __fadd_rn(pa[x], beta[x]); },
                [&](int x) { return (double)pa[x] + (double)beta[x]; }, E, k, seid + a * k, sgate + a * k,
@@ -75,11 +89,16 @@ __global__ void route_species_kernel(const float* __restrict__ Pf, const float* 
 }
 
 // Per atom: chosen experts and gates of its species.
-__global__ void route_atoms_kernel(const int* __restrict__ species, int N, int k, const int* __restrict__ seid,
+__global__ void route_atoms_kernel(const int* __restrict__ species, int N, int nsp, int k, const int* __restrict__ seid,
                                    const float* __restrict__ sgate, int* __restrict__ eid, float* __restrict__ gate) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
   const int z = species[i];
+  const long long t = blockIdx.y;
+  seid += t * nsp * k;
+  sgate += t * nsp * k;
+  eid += t * N * k;
+  gate += t * N * k;
   for (int c = 0; c < k; ++c) {
     eid[(long long)i * k + c] = seid[z * k + c];
     gate[(long long)i * k + c] = sgate[z * k + c];
@@ -94,7 +113,12 @@ __global__ void route_edges_kernel(const int* __restrict__ species, const int* _
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= Ne) return;
   const int p = species[ei[e]] * nsp + species[ej[e]];
-  pair[e] = p;
+  const long long t = blockIdx.y, np = (long long)nsp * nsp;
+  peid += t * np * k;
+  pgate += t * np * k;
+  eid += t * Ne * k;
+  gate += t * Ne * k;
+  pair[t * Ne + e] = p;
   for (int c = 0; c < k; ++c) {
     eid[(long long)e * k + c] = peid[p * k + c];
     gate[(long long)e * k + c] = pgate[p * k + c];
@@ -105,6 +129,8 @@ __global__ void route_edges_kernel(const int* __restrict__ species, const int* _
 __global__ void sort_count_kernel(const int* __restrict__ eid, long long M, int E, int* __restrict__ cnt) {
   __shared__ int hist[64];
   const int ch = blockIdx.x;
+  eid += blockIdx.y * M;
+  cnt += (long long)blockIdx.y * gridDim.x * E;
   if (threadIdx.x < 64) hist[threadIdx.x] = 0;
   __syncthreads();
   const long long f0 = (long long)ch * kSortChunk;
@@ -119,6 +145,9 @@ __global__ void sort_colscan_kernel(const int* __restrict__ cnt, int nch, int E,
                                     int* __restrict__ total) {
   __shared__ int part[256];
   const int x = blockIdx.x, t = threadIdx.x;
+  cnt += (long long)blockIdx.y * nch * E;
+  colpre += (long long)blockIdx.y * nch * E;
+  total += blockIdx.y * E;
   const int per = (nch + 255) / 256;
   const int lo = min(nch, t * per), hi = min(nch, lo + per);
   int s = 0;
@@ -139,16 +168,6 @@ __global__ void sort_colscan_kernel(const int* __restrict__ cnt, int nch, int E,
   if (t == 255) total[x] = part[255];
 }
 
-__global__ void sort_offsets_kernel(const int* __restrict__ total, int E, int* __restrict__ off) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int acc = 0;
-  for (int x = 0; x < E; ++x) {
-    off[x] = acc;
-    acc += total[x];
-  }
-  off[E] = acc;
-}
-
 // One wave per chunk walks its entries in order, 64 at a time; the rank of
 // an entry among equal keys comes from a ballot match, so the order is stable.
 __global__ __launch_bounds__(64) void sort_scatter_kernel(const int* __restrict__ eid, const float* __restrict__ gate,
@@ -157,6 +176,13 @@ __global__ __launch_bounds__(64) void sort_scatter_kernel(const int* __restrict_
                                                           float* __restrict__ slot_gate) {
   __shared__ int run[64];
   const int ch = blockIdx.x, lane = threadIdx.x;
+  const long long t = blockIdx.y;
+  eid += t * M;
+  gate += t * M;
+  off += t * (E + 1);
+  colpre += t * gridDim.x * E;
+  pos += t * M;
+  slot_gate += t * M;
   run[lane] = 0;
   __syncthreads();
   const long long f0 = (long long)ch * kSortChunk;
@@ -186,37 +212,39 @@ __global__ __launch_bounds__(64) void sort_scatter_kernel(const int* __restrict_
   }
 }
 
-void route_block(hipStream_t st, const RouteArgs& a) {
+void route_blocks(hipStream_t st, const RouteArgs& a, const TableJob& tables) {
   const int np = a.nsp * a.nsp;
-  hipLaunchKernelGGL(route_pairs_kernel, dim3(cdiv(np, 128)), dim3(128), 0, st, a.Pc, a.Pn, a.beta, a.nsp, a.E, a.k,
-                     a.peid, a.pgate, a.pprob);
+  hipLaunchKernelGGL(route_pairs_kernel, dim3(cdiv(np, 128), a.T), dim3(128), 0, st, a.Pc, a.Pn, a.beta, a.nsp, a.E,
+                     a.k, a.peid, a.pgate, a.pprob, a.wstride);
   if (a.Ne > 0)
-    hipLaunchKernelGGL(route_edges_kernel, dim3(cdiv(a.Ne, 256)), dim3(256), 0, st, a.species, a.ei, a.ej, a.Ne,
+    hipLaunchKernelGGL(route_edges_kernel, dim3(cdiv(a.Ne, 256), a.T), dim3(256), 0, st, a.species, a.ei, a.ej, a.Ne,
                        a.nsp, a.k, a.peid, a.pgate, a.pair, a.eid, a.gate);
-  sort_tokens(st, a.eid, a.gate, (long long)a.Ne * a.k, a.E, a.cnt, a.colpre, a.total, a.off, a.pos, a.slot_gate);
+  sort_tokens(st, a.eid, a.gate, (long long)a.Ne * a.k, a.E, a.cnt, a.colpre, a.total, a.off, a.pos, a.slot_gate,
+              tables, a.T);
 }
 
-void route_atoms(hipStream_t st, const AtomRouteArgs& a) {
-  hipLaunchKernelGGL(route_species_kernel, dim3(cdiv(a.nsp, 64)), dim3(64), 0, st, a.Pf, a.beta, a.nsp, a.E, a.k,
-                     a.seid, a.sgate, a.sprob);
+void route_atoms(hipStream_t st, const AtomRouteArgs& a, const TableJob& tables) {
+  hipLaunchKernelGGL(route_species_kernel, dim3(cdiv(a.nsp, 64), a.T), dim3(64), 0, st, a.Pf, a.beta, a.nsp, a.E, a.k,
+                     a.seid, a.sgate, a.sprob, a.wstride);
   if (a.N > 0)
-    hipLaunchKernelGGL(route_atoms_kernel, dim3(cdiv(a.N, 256)), dim3(256), 0, st, a.species, a.N, a.k, a.seid,
-                       a.sgate, a.eid, a.gate);
-  sort_tokens(st, a.eid, a.gate, (long long)a.N * a.k, a.E, a.cnt, a.colpre, a.total, a.off, a.pos, a.slot_gate);
+    hipLaunchKernelGGL(route_atoms_kernel, dim3(cdiv(a.N, 256), a.T), dim3(256), 0, st, a.species, a.N, a.nsp, a.k,
+                       a.seid, a.sgate, a.eid, a.gate);
+  sort_tokens(st, a.eid, a.gate, (long long)a.N * a.k, a.E, a.cnt, a.colpre, a.total, a.off, a.pos, a.slot_gate,
+              tables, a.T);
 }
 
 void sort_tokens(hipStream_t st, const int* eid, const float* gate, long long M, int E, int* cnt, int* colpre,
-                 int* total, int* off, int* pos, float* slot_gate) {
+                 int* total, int* off, int* pos, float* slot_gate, const TableJob& tables, int T) {
   const int nch = (int)((M + kSortChunk - 1) / kSortChunk);
   if (nch > 0) {
-    hipLaunchKernelGGL(sort_count_kernel, dim3(nch), dim3(256), 0, st, eid, M, E, cnt);
-    hipLaunchKernelGGL(sort_colscan_kernel, dim3(E), dim3(256), 0, st, cnt, nch, E, colpre, total);
+    hipLaunchKernelGGL(sort_count_kernel, dim3(nch, T), dim3(256), 0, st, eid, M, E, cnt);
+    hipLaunchKernelGGL(sort_colscan_kernel, dim3(E, T), dim3(256), 0, st, cnt, nch, E, colpre, total);
   } else {
-    hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, total, E);
+    hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, total, T * E);
   }
-  hipLaunchKernelGGL(sort_offsets_kernel, dim3(1), dim3(1), 0, st, total, E, off);
+  build_tables(st, tables, T);
   if (nch > 0)
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nch), dim3(64), 0, st, eid, gate, M, E, off, colpre, pos,
+    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nch, T), dim3(64), 0, st, eid, gate, M, E, off, colpre, pos,
                        slot_gate);
 }
 

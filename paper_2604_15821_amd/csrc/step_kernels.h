@@ -622,8 +622,14 @@ __global__ void router_atom_kernel(const int* __restrict__ rowptr, const int* __
 // column t % cols and the atoms g, g + G, ... of the species (g = t / cols,
 // G = 256 / cols groups, in atom order); the G group sums of a column are then
 // added in group order.
-__global__ void species_rows_kernel(const int* __restrict__ sp_off, const int* __restrict__ sp_atoms,
-                                    const float* __restrict__ M, int w, int nsp, float* __restrict__ out) {
+struct SpeciesRows {   // up to three tables of the same width, one per blockIdx.y
+  const float* M[3];
+  float* out[3];
+};
+__global__ void species_rows_kernel(const int* __restrict__ sp_off, const int* __restrict__ sp_atoms, SpeciesRows tab,
+                                    int w, int nsp) {
+  const float* __restrict__ M = tab.M[blockIdx.y];
+  float* __restrict__ out = tab.out[blockIdx.y];
   __shared__ float red[256];
   const int s = blockIdx.x;
   if (s >= nsp) return;
@@ -963,7 +969,6 @@ struct Plan {
   WChunk* chunks;
   int *nchunks, *cfirst;
   // dense tables: atoms (group of N rows) and edges (group of Ne rows)
-  int *rowN, *rowE;
   RowsTile* tilesN;
   int* ntN;
   WChunk *chunksN, *chunksE;
@@ -991,7 +996,6 @@ struct Plan {
   int* ntiles3;
   WChunk* chunks3;
   int *nchunks3, *cfirst3;
-  int *rowT;
   WChunk* chunksT;
   int *ncT, *cfT;
   // loss gradient in positions with the bond-angle term: row tiles over the
@@ -1117,16 +1121,14 @@ size_t plan_layout(Plan& p, void* base, const janus_config& c, int N, int S, lon
   p.slot_gate = cv.take<float>(T * M);
   p.total = cv.take<int>(T * E);
   p.off = cv.take<int>(T * (E + 1));
-  p.cnt = cv.take<int>((long long)p.nch * E + 1);
-  p.colpre = cv.take<int>((long long)p.nch * E + 1);
+  p.cnt = cv.take<int>((long long)T * p.nch * E + 1);
+  p.colpre = cv.take<int>((long long)T * p.nch * E + 1);
   p.tiles = cv.take<RowsTile>((long long)T * p.mt);
   p.ntiles = cv.take<int>(T + 1);
   p.chunks = cv.take<WChunk>((long long)T * p.mc);
   p.nchunks = cv.take<int>(T + 1);
   p.cfirst = cv.take<int>(T * (E + 1) + 1);
 
-  p.rowN = cv.take<int>(2);
-  p.rowE = cv.take<int>(2);
   p.tilesN = cv.take<RowsTile>(p.mtN);
   p.ntN = cv.take<int>(1);
   p.chunksN = cv.take<WChunk>(p.mcN);
@@ -1243,14 +1245,13 @@ size_t plan_layout(Plan& p, void* base, const janus_config& c, int N, int S, lon
     p.g3t = cv.take<float>(T * M3 + 1);
     p.total3 = cv.take<int>(T * E3);
     p.off3 = cv.take<int>(T * (E3 + 1));
-    p.cnt3 = cv.take<int>((long long)p.nch3 * E3 + 1);
-    p.colpre3 = cv.take<int>((long long)p.nch3 * E3 + 1);
+    p.cnt3 = cv.take<int>((long long)T * p.nch3 * E3 + 1);
+    p.colpre3 = cv.take<int>((long long)T * p.nch3 * E3 + 1);
     p.tiles3 = cv.take<RowsTile>((long long)T * p.mt3);
     p.ntiles3 = cv.take<int>(T + 1);
     p.chunks3 = cv.take<WChunk>((long long)T * p.mc3);
     p.nchunks3 = cv.take<int>(T + 1);
     p.cfirst3 = cv.take<int>(T * (E3 + 1) + 1);
-    p.rowT = cv.take<int>(2);
     p.chunksT = cv.take<WChunk>(p.mcT);
     p.mtT = max_rows_tiles(Ntt, 1);
     p.tilesT = pos_grad ? cv.take<RowsTile>(p.mtT) : nullptr;
@@ -1296,8 +1297,8 @@ size_t plan_layout(Plan& p, void* base, const janus_config& c, int N, int S, lon
     p.g3f = cv.take<float>(T * Mf + 1);
     p.totalf = cv.take<int>(T * Ef);
     p.offf = cv.take<int>(T * (Ef + 1));
-    p.cntf = cv.take<int>((long long)p.nchf * Ef + 1);
-    p.colpref = cv.take<int>((long long)p.nchf * Ef + 1);
+    p.cntf = cv.take<int>((long long)T * p.nchf * Ef + 1);
+    p.colpref = cv.take<int>((long long)T * p.nchf * Ef + 1);
     p.tilesf = cv.take<RowsTile>((long long)T * p.mtf);
     p.ntilesf = cv.take<int>(T + 1);
     p.chunksf = cv.take<WChunk>((long long)T * p.mcf);
@@ -1381,15 +1382,6 @@ __global__ void fill_kernel(float* __restrict__ out, long long n, float v) {
 __global__ void iota_kernel(int* __restrict__ out, int n) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q <= n) out[q] = q;
-}
-
-__global__ void set_rows_kernel(int* rowN, int N, int* rowE, long long Ne) {
-  if (threadIdx.x == 0) {
-    rowN[0] = 0;
-    rowN[1] = N;
-    rowE[0] = 0;
-    rowE[1] = (int)Ne;
-  }
 }
 
 }  // namespace janus
