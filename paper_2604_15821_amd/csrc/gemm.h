@@ -93,13 +93,50 @@ constexpr int SP_PLANE = 4 * SP_OCT;
 constexpr int SP_OPER = 2 * SP_PLANE;
 constexpr int SP_STAGE = 2 * SP_OPER;
 constexpr int SMEM_BODY = cmax(2 * SP_STAGE / 4, SMEM_FP32);   // floats
-constexpr int SMEM_FLOATS = SMEM_BODY + GBM + GBN + 4;   // + row and column exponents, flags
+constexpr int SMEM_FLOATS = (SMEM_BODY + GBM + GBN + 4 + 63) / 64 * 64;   // + row and column exponents, flags
+
+// How a row product multiplies: fp32 instructions, split products, or split products on tiles of 64
+// rows (a wave owns 32 x 64).
+enum { kModeFp32 = 0, kModeSplit = 1, kModeHalfRows = 2 };
 
 struct RowsTile {   // one 128-row tile of a group
   int group;
   int r0;           // first row (global)
   int r1;           // one past the last row of the group
   int pad;
+};
+
+// Where a row product finds its tiles: a table, or (tiles null) the row offsets of at most 64
+// groups, from which every wave works out its tile: 0.3 us per workgroup in place of a launch.
+struct RowsTable {
+  const RowsTile* tiles;
+  const int* n_tiles;
+  const int* off;
+  int groups;
+  __device__ __forceinline__ bool find(int t, RowsTile& out) const {
+    if (tiles) {
+      if (t >= *n_tiles) return false;
+      out = tiles[t];
+      return true;
+    }
+    const int l = threadIdx.x & 63;
+    const int a = off[l < groups ? l : groups], b = off[l < groups ? l + 1 : groups];
+    const int c = (b - a + GBM - 1) / GBM;
+    int inc = c;   // tiles of groups 0..l
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(inc, o, 64);
+      if (l >= o) inc += v;
+    }
+    const unsigned long long m = __ballot(inc > t);
+    if (!m) return false;
+    const int g = __builtin_ctzll(m);
+    out.group = g;
+    out.r0 = __builtin_amdgcn_readlane(a, g) + (t - __builtin_amdgcn_readlane(inc - c, g)) * GBM;
+    out.r1 = __builtin_amdgcn_readlane(b, g);
+    out.pad = 0;
+    return true;
+  }
 };
 
 __device__ __forceinline__ float4 f4zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
@@ -447,9 +484,10 @@ __device__ __forceinline__ void direct_km(const float* __restrict__ p, long long
 }
 __device__ __forceinline__ void wait_direct() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[2][2]) {
+template <int BI>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[BI][2]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < BI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -531,37 +569,39 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float* p, long
 //
 // Operand stored k-contiguous: thread q takes k-quad q % 8 of rows q / 8 + 32 i, so that eight
 // lanes read one row's 128 bytes.  Rows past the end read the last one (their products are never stored).
-template <class L>
+// R: loads per thread, 32 R rows.
+template <class L, int R = 4>
 struct SplitMK {
+  static constexpr int kPieces = R;
   static constexpr bool kPaired = false;   // position of row m in the tile: m
-  using Values = float4[4];
+  using Values = float4[R];
   const L& ld;
   __amdgpu_buffer_rsrc_t rs;
-  int vo[4];
-  float4 raw[4];
-  float s[4];
+  int vo[R];
+  float4 raw[R];
+  float s[R];
   __device__ __forceinline__ SplitMK(const L& l, int r0, int r1, int, int, int tid) : ld(l) {
-    const int n = r1 - r0 < GBM ? r1 - r0 : GBM;
+    const int n = r1 - r0 < 32 * R ? r1 - r0 : 32 * R;
     rs = buffer_of(l.base() + (long long)r0 * l.ld, 4LL * n * l.ld);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < R; ++i) {
       const int r = (tid >> 3) + 32 * i;
       vo[i] = 4 * ((r < n ? r : n - 1) * (int)l.ld + 4 * (tid & 7));
     }
   }
   __device__ __forceinline__ void load(int k) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < R; ++i)
       raw[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[i], 4 * k, 0));
   }
   __device__ __forceinline__ void values(int k, int tid, Values& x) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = ld.apply(raw[i], k + 4 * (tid & 7));
+    for (int i = 0; i < R; ++i) x[i] = ld.apply(raw[i], k + 4 * (tid & 7));
   }
   __device__ __forceinline__ static void publish(const Values&, float*, int) {}
   __device__ __forceinline__ void scales(const Values& x, const float*, int* ex, int tid) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < R; ++i) {
       float m = fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
 #pragma unroll
       for (int o = 1; o < 8; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
@@ -586,7 +626,7 @@ struct SplitMK {
   }
   __device__ __forceinline__ void store_all(const Values& x, char* d, int tid) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) store(i, x[i], d, tid);
+    for (int i = 0; i < R; ++i) store(i, x[i], d, tid);
   }
 };
 
@@ -597,6 +637,7 @@ struct SplitMK {
 template <class L>
 struct SplitKM {
   static constexpr bool kPaired = true;
+  static constexpr int kPieces = 4;
   using Values = float2[8];
   const L& ld;
   __amdgpu_buffer_rsrc_t rs;
@@ -686,45 +727,48 @@ struct SplitKM {
   }
 };
 
-// One stage of split products: per 32 x 32 block and 16 k, hi += h h' and lo += h l' + l h'.  After
-// every third of the 24 matrix instructions piece(0..7) runs: the conversion of the next stage in
-// eight parts, spread so that the vector units work while the matrix unit does.
-template <class F>
-__device__ __forceinline__ void split_stage(const char* st, int wm, int wn, int lr, int hf, f32x16 (&hi)[2][2],
-                                            f32x16 (&lo)[2][2], const F& piece) {
-  f16x8 a[2][2], b[2][2];
+// One stage of split products: per 32 x 32 block and 16 k, hi += h h' and lo += h l' + l h'.  Between
+// the 12 BI matrix instructions piece(0..NP - 1) run at equal distances: the conversion of the next
+// stage in parts, spread so that the vector units work while the matrix unit does.
+template <int BI, int NP, class F>
+__device__ __forceinline__ void split_stage(const char* st, int wm, int wn, int lr, int hf, f32x16 (&hi)[BI][2],
+                                            f32x16 (&lo)[BI][2], const F& piece) {
+  constexpr int kEvery = 12 * BI / NP;
+  f16x8 a[BI][2], b[2][2];
 #pragma unroll
-  for (int q = 0; q < 24; ++q) {
-    const int g = q / 12, t = q / 4 % 3, bi = q / 2 % 2, bj = q % 2;
-    if (q % 12 == 0) {
+  for (int q = 0; q < 12 * BI; ++q) {
+    const int g = q / (6 * BI), t = q / (2 * BI) % 3, bi = q / 2 % BI, bj = q % 2;
+    if (q % (6 * BI) == 0) {
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
+      for (int p = 0; p < 2; ++p) {
+        const char* o = st + p * SP_PLANE + (2 * g + hf) * SP_OCT;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const char* o = st + p * SP_PLANE + (2 * g + hf) * SP_OCT;
-          a[c][p] = *reinterpret_cast<const f16x8*>(o + (wm * 64 + c * 32 + lr) * 16);
+        for (int c = 0; c < BI; ++c)
+          a[c][p] = *reinterpret_cast<const f16x8*>(o + (wm * 32 * BI + c * 32 + lr) * 16);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
           b[c][p] = *reinterpret_cast<const f16x8*>(o + SP_OPER + (wn * 64 + c * 32 + lr) * 16);
-        }
+      }
     }
     if (t == 0)
       hi[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][0], b[bj][0], hi[bi][bj], 0, 0, 0);
     else
       lo[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][t == 2], b[bj][t == 1], lo[bi][bj], 0, 0, 0);
-    if (q % 3 == 2) piece(q / 3);
+    if (q % kEvery == kEvery - 1) piece(q / kEvery);
   }
 }
 
 // The K loop of the split products over [kb, ke).  A and B: loader, first and last row (column)
 // of the tile's operand.  On return hi holds h h' + 2^-11 (h l' + l h') of the scaled operands and
 // smem the exponents that undo the scales; false if a value is not finite.
-template <class SA, class SB, class LA, class LB>
+template <class SA, class SB, int BI, class LA, class LB>
 __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, int a1, const LB& bl, int b0, int b1,
                                            int kb, int ke, int wm, int wn, int lr, int hf, int tid,
-                                           f32x16 (&hi)[2][2]) {
+                                           f32x16 (&hi)[BI][2]) {
   char* lds = reinterpret_cast<char*>(smem);
   int* ex = reinterpret_cast<int*>(smem + SMEM_BODY);   // [128] rows, [128] columns
   float* flag = smem + SMEM_BODY + GBM + GBN;
-  f32x16 lo[2][2];
+  f32x16 lo[BI][2];
   zero_acc(hi);
   zero_acc(lo);
   SA sa(al, a0, a1, kb, ke, tid);
@@ -756,19 +800,19 @@ __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, in
   for (int k = kb; k < last; k += SBK) {
     char* d = lds + (cur ^ 1) * SP_STAGE;
     const int next = k1 + SBK < last ? k1 + SBK : last;
-    split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [&](int n) {
-      if (n < 4) sa.piece(n, k1, next, d, tid); else sb.piece(n - 4, k1, next, d + SP_OPER, tid);
+    split_stage<BI, SA::kPieces + SB::kPieces>(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [&](int n) {
+      if (n < SA::kPieces) sa.piece(n, k1, next, d, tid); else sb.piece(n - SA::kPieces, k1, next, d + SP_OPER, tid);
       __builtin_amdgcn_sched_barrier(0);   // keeps the parts where they are
     });
     k1 = next;
     __syncthreads();
     cur ^= 1;
   }
-  split_stage(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [](int) {});
+  split_stage<BI, 1>(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [](int) {});
   __syncthreads();
   float z = 0.f;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < BI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -783,13 +827,14 @@ __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, in
 }
 
 // Undo the scales: acc[bi][bj][v] is row 32 bi + 8 (v / 4) + 4 hf + v % 4, column 32 bj + lr of the wave.
-__device__ __forceinline__ void unscale(const float* smem, int wm, int wn, int lr, int hf, f32x16 (&acc)[2][2]) {
+template <int BI>
+__device__ __forceinline__ void unscale(const float* smem, int wm, int wn, int lr, int hf, f32x16 (&acc)[BI][2]) {
   const int* ex = reinterpret_cast<const int*>(smem + SMEM_BODY);
 #pragma unroll
-  for (int bi = 0; bi < 2; ++bi)
+  for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4) {
-      const int4 er = *reinterpret_cast<const int4*>(ex + wm * 64 + bi * 32 + 8 * v4 + 4 * hf);
+      const int4 er = *reinterpret_cast<const int4*>(ex + wm * 32 * BI + bi * 32 + 8 * v4 + 4 * hf);
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj) {
         const int ec = ex[128 + wn * 64 + bj * 32 + lr];
@@ -851,32 +896,40 @@ __device__ __forceinline__ void rows_fp32(float* smem, const ALoad& al, const fl
   }
 }
 
-// The same on split products; false (and acc undefined) if a value is infinite or not a number.
-template <bool NT, class ALoad>
+// The same on split products, for a tile of 64 BI rows; false (and acc undefined) if a value is
+// infinite or not a number.
+template <bool NT, int BI, class ALoad>
 __device__ __forceinline__ bool rows_split(float* smem, const ALoad& al, const float* __restrict__ Bg, int K, int N,
                                            int r0, int r1, int n0, int wm, int wn, int lr, int hf, int tid,
-                                           f32x16 (&acc)[2][2]) {
+                                           f32x16 (&acc)[BI][2]) {
   const LoadPlain bl{Bg, NT ? K : N};
+  using SA = SplitMK<ALoad, 2 * BI>;
   using SB = std::conditional_t<NT, SplitMK<LoadPlain>, SplitKM<LoadPlain>>;
-  if (!split_loop<SplitMK<ALoad>, SB>(smem, al, r0, r1, bl, n0, N, 0, K, wm, wn, lr, hf, tid, acc)) return false;
-  unscale(smem, wm, wn, lr, hf, acc);
+  if (!split_loop<SA, SB, BI>(smem, al, r0, r1, bl, n0, N, 0, K, wm, wn, lr, hf, tid, acc)) return false;
+  unscale<BI>(smem, wm, wn, lr, hf, acc);
   return true;
 }
 
 // One output tile of gemm_rows for (XCD-mapped) block number vb; smem holds
 // SMEM_FLOATS floats of LDS.
-template <bool NT, class ALoad, class Epi, bool Split>
+template <bool NT, class ALoad, class Epi, int Mode>
 __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad& al, const float* __restrict__ B,
-                                                int K, int N, const RowsTile* __restrict__ tiles,
-                                                const int* __restrict__ n_tiles, const Epi& epi,
+                                                int K, int N, const RowsTable& table, const Epi& epi,
                                                 float* __restrict__ rowsum_out) {
+  constexpr int BI = Mode == kModeHalfRows ? 1 : 2;
   const int ncol = (N + GBN - 1) / GBN;
   int t, ctile;
-  xcd_map(vb, ncol, t, ctile);
-  if (t >= *n_tiles) return;
-  const RowsTile tile = tiles[t];
+  xcd_map(vb, BI == 1 ? 2 * ncol : ncol, t, ctile);
+  RowsTile tile;
+  if (!table.find(t, tile)) return;
+  int r0 = tile.r0, r1 = tile.r1;
+  if (BI == 1) {   // the upper or lower 64 rows of the tile
+    r0 += 64 * (ctile & 1);
+    ctile >>= 1;
+    if (r0 >= r1) return;
+    r1 = r1 < r0 + 64 ? r1 : r0 + 64;
+  }
   const int n0 = ctile * GBN;
-  const int r0 = tile.r0, r1 = tile.r1;
   const float* Bg = B + (long long)tile.group * K * N;
 
   const int tid = threadIdx.x;
@@ -886,12 +939,22 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
 
   f32x16 acc[2][2];
   bool paired = false;   // columns of the two blocks: 2 lr and 2 lr + 1 (else lr and 32 + lr)
-  if constexpr (Split) {
-    paired = rows_split<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
-    if (!paired) rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
-    paired = paired && !NT;
-  } else {
+  bool wide = true;      // a wave holds 64 rows (else 32, in acc[0])
+  if constexpr (Mode == kModeFp32) {
     rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+  } else {
+    bool done;
+    if constexpr (BI == 1) {
+      f32x16 a1[1][2];
+      done = rows_split<NT, 1>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, a1);
+      acc[0][0] = a1[0][0];
+      acc[0][1] = a1[0][1];
+      wide = !done;
+    } else {
+      done = rows_split<NT, 2>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+    }
+    if (!done) rows_fp32<NT>(smem, al, Bg, K, N, r0, r1, n0, wm, wn, lr, hf, tid, acc);
+    paired = done && !NT;
   }
 
   // Epilogue in two halves of 64 rows: the waves of row half `half` stage
@@ -900,16 +963,20 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
   // two batches: first the batch's global reads, then arithmetic and stores.
   float* sC = smem;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    if (wm == half) {
+  for (int half = 0; half < BI; ++half) {
+    auto stage = [&](int bi, int row) {
 #pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
+      for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            sC[(bi * 32 + 8 * (v >> 2) + 4 * hf + (v & 3)) * LD_C + wn * 64 + (paired ? 2 * lr + bj : bj * 32 + lr)] =
-                acc[bi][bj][v];
+        for (int v = 0; v < 16; ++v)
+          sC[(row + 8 * (v >> 2) + 4 * hf + (v & 3)) * LD_C + wn * 64 + (paired ? 2 * lr + bj : bj * 32 + lr)] =
+              acc[bi][bj][v];
+    };
+    if (BI == 1 && !wide) {
+      stage(0, 32 * wm);
+    } else if (wm == half) {
+      stage(0, 0);
+      stage(1, 32);
     }
     // 4 pieces per batch; loads past the range read the last valid row.
     const int c4 = tid & 31;
@@ -941,13 +1008,12 @@ __device__ __forceinline__ void gemm_rows_block(int vb, float* smem, const ALoad
   }
 }
 
-template <bool NT, class ALoad, class Epi, bool Split>
-__global__ __launch_bounds__(256, 2) void gemm_rows_kernel(ALoad al, const float* __restrict__ B, int K, int N,
-                                                           const RowsTile* __restrict__ tiles,
-                                                           const int* __restrict__ n_tiles, Epi epi,
-                                                           float* __restrict__ rowsum_out) {
-  __shared__ __attribute__((aligned(16))) float smem[Split ? SMEM_FLOATS : SMEM_FP32];
-  gemm_rows_block<NT, ALoad, Epi, Split>(blockIdx.x, smem, al, B, K, N, tiles, n_tiles, epi, rowsum_out);
+template <bool NT, class ALoad, class Epi, int Mode>
+__global__ __launch_bounds__(256, 2) void gemm_rows_kernel(
+    ALoad al, const float* __restrict__ B, int K, int N, RowsTable table, Epi epi, float* __restrict__ rowsum_out) {
+  __shared__ __attribute__((aligned(16)))
+  float smem[Mode == kModeFp32 ? SMEM_FP32 : SMEM_FLOATS];
+  gemm_rows_block<NT, ALoad, Epi, Mode>(blockIdx.x, smem, al, B, K, N, table, epi, rowsum_out);
 }
 
 // --------------------------------------------------------------- gemm_wgrad
@@ -1019,9 +1085,9 @@ template <class ALoad, class BLoad>
 __device__ __forceinline__ bool wgrad_split(float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
                                             const WChunk& ch, int p0, int q0, int wm, int wn, int lr, int hf, int tid,
                                             f32x16 (&acc)[2][2]) {
-  if (!split_loop<SplitKM<ALoad>, SplitKM<BLoad>>(smem, al, p0, P, bl, q0, Q, ch.r0, ch.r1, wm, wn, lr, hf, tid, acc))
+  if (!split_loop<SplitKM<ALoad>, SplitKM<BLoad>, 2>(smem, al, p0, P, bl, q0, Q, ch.r0, ch.r1, wm, wn, lr, hf, tid, acc))
     return false;
-  unscale(smem, wm, wn, lr, hf, acc);
+  unscale<2>(smem, wm, wn, lr, hf, acc);
   return true;
 }
 

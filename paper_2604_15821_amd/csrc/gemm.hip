@@ -137,6 +137,21 @@ void build_tables(hipStream_t st, const TableJobs& jobs, int n_jobs, int n_block
   hipLaunchKernelGGL(build_tables_kernel, dim3(n_jobs, n_blocks), dim3(256), 0, st, jobs);
 }
 
+// The standalone product.  Up to 64 groups and four rounds of resident workgroups, each works its
+// tile out of the offsets (no table launch, about 4 us); a longer grid reads it from a table.
+static void grouped_rows(hipStream_t st, const float* A, const float* B, float* C, const int32_t* row_off,
+                         int n_groups, int K, int N, int trans_b, RowsTile* tiles, int* nt, int mt) {
+  RowsTable table{tiles, nt, row_off, n_groups};
+  if (n_groups <= 64 && (long long)mt * ((N + GBN - 1) / GBN) <= 2048)
+    table.tiles = nullptr;
+  else
+    build_tables(st, tables_of(row_off, n_groups).rows_tiles(tiles, nt));
+  if (trans_b)
+    launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, table, mt, EpiStore{C, N});
+  else
+    launch_rows<false>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, table, mt, EpiStore{C, N});
+}
+
 int ensure(janus_buffer& b, size_t bytes) {
   if (bytes <= b.bytes && b.ptr) return JANUS_OK;
   if (b.ptr) {
@@ -175,11 +190,7 @@ extern "C" int janus_grouped_gemm(janus_ctx* ctx, const float* A, const float* B
   Carver c2(ctx->aux.ptr);
   RowsTile* tiles = c2.take<RowsTile>(mt);
   int* nt = c2.take<int>(1);
-  build_tables(st, tables_of(row_off, n_groups).rows_tiles(tiles, nt));
-  if (trans_b)
-    launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
-  else
-    launch_rows<false>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+  grouped_rows(st, A, B, C, row_off, n_groups, K, N, trans_b, tiles, nt, mt);
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
 }
@@ -238,11 +249,7 @@ extern "C" int janus_grouped_gemm_noalloc(const float* A, const float* B, float*
   if (cv.size() > kNoAllocScratchBytes) return JANUS_ENOMEM;
   // the table kernel rewrites the count and every tile the launch reads, so
   // nothing left by an earlier call is used
-  build_tables(st, tables_of(row_off, n_groups).rows_tiles(tiles, nt));
-  if (trans_b)
-    launch_rows<true>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
-  else
-    launch_rows<false>(std::true_type{}, st, LoadPlain{A, K}, B, K, N, tiles, nt, mt, EpiStore{C, N});
+  grouped_rows(st, A, B, C, row_off, n_groups, K, N, trans_b, tiles, nt, mt);
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
 }

@@ -11,7 +11,8 @@ from helpers import banner
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [130, 0, 7]
+# tiles of 64 rows (few tiles) and of 128 (more than 256 workgroups)
+SIZES = {"few": [130, 0, 7], "many": [33_000, 0, 61]}
 
 
 @pytest.fixture(scope="module")
@@ -52,19 +53,23 @@ def _run(ctx, A, B, off, trans_b):
     return out.cpu().numpy()
 
 
-@pytest.mark.parametrize("K,N", [(16, 64), (48, 192), (64, 128), (208, 320)])
+@pytest.mark.parametrize("K,N", [(16, 64), (32, 64), (48, 192), (64, 128), (224, 320)])
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("kind_a,kind_b", [("normal", "normal"), ("magnitudes", "magnitudes"), ("growth", "decay"),
                                            ("decay", "growth"), ("late", "normal"), ("normal", "late"),
                                            ("zeros", "normal")])
-def test_rows(ctx, K, N, trans_b, kind_a, kind_b):
-    banner("split rows", K, N, trans_b, kind_a, kind_b)
+@pytest.mark.parametrize("size", ["few", "many"])
+def test_rows(ctx, K, N, trans_b, kind_a, kind_b, size):
+    banner("split rows", K, N, trans_b, kind_a, kind_b, size)
+    if size == "many" and K not in (32, 64):
+        pytest.skip("covered by the other widths")
     rng = np.random.default_rng(K + N + trans_b)
-    off = np.concatenate([[0], np.cumsum(SIZES)]).astype(np.int32)
+    sizes = SIZES[size]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     A = _values(kind_a, rng, (int(off[-1]), K), 1)
-    B = _values(kind_b, rng, (len(SIZES), N, K) if trans_b else (len(SIZES), K, N), 2 if trans_b else 1)
+    B = _values(kind_b, rng, (len(sizes), N, K) if trans_b else (len(sizes), K, N), 2 if trans_b else 1)
     got = _run(ctx, A, B, off, trans_b)
-    for g in range(len(SIZES)):
+    for g in range(len(sizes)):
         a = A[off[g]:off[g + 1]].astype(np.float64)
         b = (B[g].T if trans_b else B[g]).astype(np.float64)
         bound = (K + 8) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)) + 1e-45
@@ -90,11 +95,12 @@ def test_wgrad(ctx, rows, kind_a, kind_b):
 
 
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
-def test_infinities_and_nan_stay_in_their_rows_and_columns(ctx, bad):
-    banner("split non-finite", bad)
+@pytest.mark.parametrize("rows", [200, 33_000])
+def test_infinities_and_nan_stay_in_their_rows_and_columns(ctx, bad, rows):
+    banner("split non-finite", bad, rows)
     rng = np.random.default_rng(1)
-    off = np.array([0, 200], np.int32)
-    A = rng.standard_normal((200, 96)).astype(np.float32)
+    off = np.array([0, rows], np.int32)
+    A = rng.standard_normal((rows, 96)).astype(np.float32)
     B = rng.standard_normal((1, 96, 128)).astype(np.float32) * np.float32(0.01)
     A[17, 50] = bad
     B[0, 3, 70] = bad
