@@ -31,9 +31,9 @@
 //    accumulators of their own (the matrix unit truncates small addends when it
 //    aligns them to a large accumulator, a bias that grows with the length of
 //    the contraction when both share one).  The scale comes from the largest
-//    magnitude of the row's (column's) first 32 k, brought to [2^6, 2^7): values
-//    up to 2^9 times as large fit fp16, and values down to 2^-20 of it keep all
-//    their bits, below that an absolute 2^-42 of it is lost.  A larger value (or
+//    magnitude of the row's (column's) first 32 k, brought to [1, 2): values up to
+//    2^15 times as large fit fp16, and values down to 2^-12 of it keep all
+//    their bits, below that an absolute 2^-36 of it is lost.  A larger value (or
 //    one after 32 zeros) overflows to infinity, and the tile is taken again on
 //    the fp32 instructions, as is any tile with infinities or NaN.
 //    Two workgroups per CU (about 230 registers); a stage's registers are loaded a whole
@@ -549,10 +549,14 @@ __device__ __forceinline__ void split_pair(float a, float b, float s, unsigned& 
   h = __builtin_bit_cast(unsigned, hv);
   l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2v){ra, rb}, f16x2));
 }
-// Power-of-two scale that brings a value of magnitude m to [2^6, 2^7), as its exponent field.
+// Power-of-two scale that brings a value of magnitude m to [1, 2), as its exponent field.  The lower the
+// target, the more growth fits (2^15 here) and the higher the floor below which bits are lost (2^-36 of m).
+// Short bonds make some rows far larger than the first 32 of a chunk, and a tile that overflows
+// costs a second, fp32 pass: target 2^6 (growth 2^9) 370 ms for a step of 32 mixed structures, 2^2 334, 1 325,
+// 2^-3 323; small batch 14.1, 13.4, 13.4 and 13.3 ms.
 __device__ __forceinline__ int scale_field(float m) {
-  const int f = 254 + 6 - (int)(__float_as_uint(m) >> 23);
-  return f > 254 ? 254 : f;
+  const int f = 254 - (int)(__float_as_uint(m) >> 23);
+  return f < 1 ? 1 : f;
 }
 
 // Buffer loads of the staged operands: 32-bit offsets from the tile's (uniform) base, zero past `bytes`.

@@ -34,6 +34,9 @@ def _values(kind, rng, shape, k_axis):
         x = np.ldexp(x, rng.integers(-40, 40, s))
     elif kind == "growth":         # later values 2^16 times the first ones
         x = np.where(k >= 32, np.ldexp(x, 16), x)
+    elif kind == "fits":           # later values up to just under 2^15 times the largest of the first 32
+        m = np.abs(np.where(k < 32, x, 0.0)).max(axis=k_axis, keepdims=True)
+        x = np.where(k >= 32, np.clip(x, -1.0, 1.0) * np.ldexp(m, 14), x)
     elif kind == "decay":          # later values 2^-16 of the first ones
         x = np.where(k >= 32, np.ldexp(x, -16), x)
     elif kind == "late":           # zeros in the first 32
@@ -56,7 +59,7 @@ def _run(ctx, A, B, off, trans_b):
 @pytest.mark.parametrize("K,N", [(16, 64), (32, 64), (48, 192), (64, 128), (224, 320)])
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("kind_a,kind_b", [("normal", "normal"), ("magnitudes", "magnitudes"), ("growth", "decay"),
-                                           ("decay", "growth"), ("late", "normal"), ("normal", "late"),
+                                           ("decay", "growth"), ("fits", "normal"), ("late", "normal"), ("normal", "late"),
                                            ("zeros", "normal")])
 @pytest.mark.parametrize("size", ["few", "many"])
 def test_rows(ctx, K, N, trans_b, kind_a, kind_b, size):
@@ -78,7 +81,7 @@ def test_rows(ctx, K, N, trans_b, kind_a, kind_b, size):
 
 @pytest.mark.parametrize("rows", [5, 16, 33, 700])
 @pytest.mark.parametrize("kind_a,kind_b", [("normal", "normal"), ("magnitudes", "normal"), ("growth", "decay"),
-                                           ("late", "normal"), ("normal", "zeros")])
+                                           ("fits", "normal"), ("late", "normal"), ("normal", "zeros")])
 def test_wgrad(ctx, rows, kind_a, kind_b):
     import torch
     banner("split wgrad", rows, kind_a, kind_b)
