@@ -428,9 +428,11 @@ __device__ __forceinline__ long long block_exclusive_scan(long long v, long long
   return r;
 }
 
-// The same by one workgroup, for inputs of up to kScanOne values (four rounds of 16 384): one launch
-// in place of three, each of which takes 3 to 5 us whatever its size.
-constexpr int kScanOneThreads = 1024, kScanOne = 65536;
+// The same by one workgroup, for inputs of up to kScanOne values: one launch in place of three, each
+// of which takes 3 to 5 us whatever its size.  The line lies at one round of the workgroup: with two
+// the chain of rounds costs more than it saves (whole neighbour list of 32 262 atoms 208.5 us, 202.3
+// by three launches).
+constexpr int kScanOneThreads = 1024, kScanOne = 16384;
 __global__ __launch_bounds__(kScanOneThreads) void scan_one_kernel(const int* __restrict__ in, int n,
                                                                    int* __restrict__ out, int* __restrict__ flag) {
   __shared__ long long wsum[kScanOneThreads / 64];
