@@ -178,6 +178,7 @@ struct LoadPlain {
   __device__ __forceinline__ Raw load(long long r, int k) const { return ld4(p + r * ld + k); }
   __device__ __forceinline__ float4 apply(const Raw& v, int) const { return v; }
   static constexpr bool kRowFactor = false;
+  static constexpr bool kZeroToZero = true;   // apply2 of zeros is zero (SplitKM's rows past the end)
   __device__ __forceinline__ const float* base() const { return p; }
   __device__ __forceinline__ float2 apply2(float2 v, float, int) const { return v; }
 };
@@ -206,6 +207,7 @@ struct LoadSiluRowScale {   // s[r] * SiLU(p[r, k])
     return make_float4(x.s * silu(x.v.x), x.s * silu(x.v.y), x.s * silu(x.v.z), x.s * silu(x.v.w));
   }
   static constexpr bool kRowFactor = true;   // apply2's second argument: s[r]
+  static constexpr bool kZeroToZero = true;
   __device__ __forceinline__ const float* base() const { return p; }
   __device__ __forceinline__ float2 apply2(float2 v, float f, int) const {
     return make_float2(f * silu(v.x), f * silu(v.y));
@@ -223,6 +225,7 @@ struct LoadSiluD1Scaled {   // SiLU'(z[r, k]) * w[k]
     return make_float4(silu_d1(v.x) * ww.x, silu_d1(v.y) * ww.y, silu_d1(v.z) * ww.z, silu_d1(v.w) * ww.w);
   }
   static constexpr bool kRowFactor = false;
+  static constexpr bool kZeroToZero = false;   // SiLU'(0) = 1/2
   __device__ __forceinline__ const float* base() const { return z; }
   __device__ __forceinline__ float2 apply2(float2 v, float, int k) const {
     return make_float2(silu_d1(v.x) * w[k], silu_d1(v.y) * w[k + 1]);
@@ -666,12 +669,12 @@ struct SplitKM {
   }
   __device__ __forceinline__ void load(int k) { load_rows(k, 0, 8); }
   __device__ __forceinline__ float2 value(int i, int k, int tid) const {
+    const int r = k + 8 * octet(tid) + i;
     float f = 1.f;
-    if constexpr (L::kRowFactor) {
-      const int r = k + 8 * octet(tid) + i;
-      f = ld.s[r < ke ? r : ke - 1];
-    }
-    return ld.apply2(raw[i], f, mc);
+    if constexpr (L::kRowFactor) f = ld.s[r < ke ? r : ke - 1];
+    const float2 v = ld.apply2(raw[i], f, mc);
+    // a padded row must not take part in the choice of a column's scale: loaded as zeros, it stays zero
+    return L::kZeroToZero || r < ke ? v : make_float2(0.f, 0.f);
   }
   __device__ __forceinline__ void values(int k, int tid, Values& x) const {
 #pragma unroll
