@@ -451,6 +451,14 @@ int janus_set_concurrency(janus_ctx* ctx, int on);
  *   trans_b = 0:  C[r, :] = A[r, :] (K) x B_g,   B_g = B + g*K*N stored [K, N]
  *   trans_b = 1:  C[r, :] = A[r, :] (K) x B_g^T, B_g = B + g*N*K stored [N, K]
  * A [M*K], C [M*N]; K and N multiples of 16 and 64 respectively.
+ * Accuracy: |C - exact| <= (K + 16) 2^-24 sum_k |a_k b_k| per entry, for finite results; an
+ * infinity or NaN of A (B) reaches its own row (column) only.  The error of an entry with K
+ * independent operands is well below that of a plain fp32 sum, but a single product
+ * is good to 2^-21, not to the last bit.  Where K is a multiple of 32 the operands are scaled and split into
+ * two fp16 terms each and multiplied on the 16-bit matrix units.  Tiles of 128 x 128 whose values span
+ * too wide a range for that (along K more than 2^7 times the largest of their row's or column's first 32
+ * values, first values of zero before others, or many so small that the bound above might not hold) are
+ * multiplied a second time on the fp32 matrix units and take up to three times as long.
  * Errors: JANUS_EINVAL, JANUS_EHIP.
  */
 int janus_grouped_gemm(janus_ctx* ctx, const float* A, const float* B, float* C,
@@ -462,7 +470,8 @@ int janus_grouped_gemm(janus_ctx* ctx, const float* A, const float* B, float* C,
  *   G_g[p, q] = sum over rows r of group g of  A[r, p] * B[r, q]
  * with A [M*P], B [M*Q], G [n_groups*P*Q]; P, Q multiples of 4.  Groups
  * with no rows produce exact zeros.  The sum is split over row chunks and
- * reduced in a fixed order.  Errors: JANUS_EINVAL, JANUS_EHIP.
+ * reduced in a fixed order.  Accuracy and time as for janus_grouped_gemm, with the group's rows for
+ * K and growth up to 2^15 within a chunk.  Errors: JANUS_EINVAL, JANUS_EHIP.
  */
 int janus_grouped_wgrad(janus_ctx* ctx, const float* A, const float* B, float* G,
                         const int32_t* row_off, int32_t n_groups, int64_t M, int32_t P, int32_t Q,

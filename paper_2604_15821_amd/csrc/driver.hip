@@ -207,9 +207,10 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
   if (atom) hipLaunchKernelGGL(iota_kernel, dim3(cdiv(N + 1, 256)), dim3(256), 0, st, p.iota, N);
   const bool attn = p.attn != 0;
   // Split products (half the error of the fp32 matrix instructions and up to twice their rate)
-  // for every model but those with attention: there the weight gradient amplifies any change of
-  // rounding (the step of 64 cells with 4 heads lies 2e-6 to 3e-3 from the 64-bit result,
-  // depending on the batch, with either product), so its results are kept bit for bit.
+  // for every model but those with attention: what passes through a softmax afterwards amplifies any
+  // change of rounding (the step of 64 cells with 4 heads lies 2e-6 to 3e-3 from the 64-bit result,
+  // depending on the batch, with either product), so the results of these models are kept bit for bit.
+  // (Their weight gradients, which nothing reads again, would not need that.)
   const bool split = !attn;
   // From two column tiles of dW2 (d >= 256) the product before it stores g SiLU(A) for it (EpiP4):
   // step of 32 mixed structures at d = 512 399 -> 377 ms.  With one tile SiLU is evaluated once anyway
@@ -275,7 +276,7 @@ int run_chunk(janus_ctx* ctx, hipStream_t st, Plan& p, const Layout& L, const Ch
     build_tables(st, dense, n_dense, 1);
     if (p.rf) {
       // routing on the edge tokens: the identity slot map, gates of one, the
-      // zero-padded router weights and their gradient accumulators
+      // padded router weights and their gradient accumulators
       hipLaunchKernelGGL(iota_kernel, dim3(cdiv(Ne + 1, 256)), dim3(256), 0, st, p.iotaE, (int)Ne);
       hipLaunchKernelGGL(fill_kernel, dim3(cdiv(M + 1, 256)), dim3(256), 0, st, p.ones, M + 1, 1.f);
       for (int t = 0; t < T; ++t)

@@ -23,29 +23,30 @@
 //
 //  * Split products (v_mfma_f32_32x32x16_f16).  An fp32 operand value, scaled
 //    by a power of two per row of A and per column of B, is the sum of two
-//    fp16 numbers, x s = h + 2^-11 l: h holds 11 significant bits and l the
-//    13 that are left (sign included), so nothing of a 24-bit significand is
-//    lost.  C = sum h h' + 2^-11 sum (h l' + l h') takes three 16-bit matrix
-//    products in place of one fp32 product at a sixteenth of their rate; what
-//    is left out, 2^-22 l l', is below 2^-24 of the product.  The two sums have
-//    accumulators of their own (the matrix unit truncates small addends when it
-//    aligns them to a large accumulator, a bias that grows with the length of
-//    the contraction when both share one).  The scale comes from the largest
-//    magnitude of the row's (column's) first 32 k, brought to [1, 2): values up to
-//    2^15 times as large fit fp16, and values down to 2^-12 of it keep all
-//    their bits, below that an absolute 2^-36 of it is lost.  A larger value (or
-//    one after 32 zeros) overflows to infinity, and the tile is taken again on
-//    the fp32 instructions, as is any tile with infinities or NaN.
-//    Two workgroups per CU (about 230 registers); a stage's registers are loaded a whole
+//    fp16 numbers, x s = h + 2^-11 l, to 2^-23 of itself: h and l hold 11 significant bits each and l
+//    its sign, 23 of the 24 bits (a quarter of all values lose the last one).  C = sum h h' +
+//    2^-11 sum (h l' + l h') takes three 16-bit matrix products in place of one fp32 product at a
+//    sixteenth of their rate; what is left out, 2^-22 l l', is up to 2^-22 of a product (root mean square
+//    2^-24.6).  The two sums have accumulators of their own (the matrix unit truncates small addends when
+//    it aligns them to a large accumulator, a bias that grows with the length of the contraction when both
+//    share one).  Each product is thus good to about 2^-21 where fp32 is to 2^-24, and a sum of many is nearer to
+//    the 64-bit result than on the fp32 instructions, because there are fewer and smaller roundings as it adds up:
+//    relative error (2-norm) at K = 128 / 512 / 2048: 1.1 / 1.7 / 3.0e-7, fp32 instructions 2.0 / 4.1 / 8.1e-7.
+//    The scale comes from the largest magnitude of the row's (column's) first 32 k and bounds the range:
+//    row products take values from 2^-21 to 2^7 times that magnitude with all these bits, weight gradients from
+//    2^-13 to 2^15 (scale_field).  A larger value (or one after 32 zeros) overflows to infinity, and the
+//    tile is taken again on the fp32 instructions, as is any tile with infinities or NaN.  A smaller
+//    value loses bits; where that can matter (LowCount) the tile is taken again as well.
+//    Two workgroups per CU (about 250 registers); a stage's registers are loaded a whole
 //    stage before they are converted, and the conversion runs in eight parts between the matrix
 //    instructions, so that vector and matrix units work at once.  Left for the end of a stage, on
 //    loads issued at its beginning, the conversion made the stage a serial chain: K = 512, N = 2048
-//    208 TFLOP/s (NN) and 242 (NT), weight gradient 178, against 266, 281 and 248 now.
+//    208 TFLOP/s (NN) and 242 (NT), weight gradient 178, against 266, 281 and 248.
 //    Measured against the fp32 instructions, 500 000 rows over 64 groups: K = 512,
-//    N = 2048 132 -> 266 TFLOP/s (NN), 135 -> 281 (NT); K = 2048, N = 512 133 -> 305
-//    and 137 -> 321; weight gradient 512 x 2048 114 -> 248; 340 000 rows over 8 groups,
-//    128 x 512: 111 -> 163, 113 -> 168 and 104 -> 162 (0.87 GB in 266-275 us).  Error against 64 bits at K = 128 / 512 / 2048: 1.1 / 1.7 / 3.0e-7,
-//    fp32 instructions 2.0 / 4.1 / 8.1e-7.  Three bf16 terms and six products, which need no
+//    N = 2048 126 -> 242 TFLOP/s (NN), 128 -> 258 (NT); K = 2048, N = 512 130 -> 292
+//    and 130 -> 299; weight gradient 512 x 2048 115 -> 223; 340 000 rows over 8 groups,
+//    128 x 512: 108 -> 171, 113 -> 167 and 107 -> 160 (0.87 GB in 260-278 us).
+//    Three bf16 terms and six products, which need no
 //    scale, reach 131-190 and 121-140 TFLOP/s (with the unspread conversion): the six products
 //    bring the clock down to 1.7 GHz.
 //
@@ -93,7 +94,8 @@ constexpr int SP_PLANE = 4 * SP_OCT;
 constexpr int SP_OPER = 2 * SP_PLANE;
 constexpr int SP_STAGE = 2 * SP_OPER;
 constexpr int SMEM_BODY = cmax(2 * SP_STAGE / 4, SMEM_FP32);   // floats
-constexpr int SMEM_FLOATS = (SMEM_BODY + GBM + GBN + 4 + 63) / 64 * 64;   // + row and column exponents, flags
+// + exponents, low counts and largest values of the rows and columns, flags
+constexpr int SMEM_FLOATS = SMEM_BODY + 3 * (GBM + GBN) + 64;
 
 // How a row product multiplies: fp32 instructions, split products, or split products on tiles of 64
 // rows (a wave owns 32 x 64).
@@ -539,27 +541,52 @@ __device__ __forceinline__ void mfma_stage(const float* a_s, const float* b_s, i
 }
 
 // ---------------------------------------------------------- split products
-// Split of a scaled value: x s = h + 2^-11 l with h, l in fp16, each rounded to nearest.  h
-// holds 11 significant bits and l the 13 that are left, so the split of a normal x is exact.
+// Split of a scaled value: x s = h + 2^-11 l with h, l in fp16, each rounded to nearest.  h holds 11
+// significant bits; what is left has 12 and its sign, of which l holds 11.
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split_pair(float a, float b, float s, unsigned& h, unsigned& l) {
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// What LowCount adds up.  top: the largest |x|; low: sum of the low weights, in 2048ths.
+__device__ __forceinline__ void count_pair(float a, float b, unsigned h, float& top, unsigned& low) {
+  top = fmaxf(fmaxf(top, fabsf(a)), fabsf(b));
+  // fp16 numbers up to 2^-13 (0x0800) are proportional to their bits
+  const u16x2 u = __builtin_elementwise_min(__builtin_bit_cast(u16x2, h & 0x7fff7fffu), (u16x2){0x800, 0x800});
+  low = __builtin_amdgcn_sad_u16(__builtin_bit_cast(unsigned, u), 0x08000800u, low);
+}
+template <bool Count>
+__device__ __forceinline__ void split_pair(float a, float b, float s, unsigned& h, unsigned& l, float& top,
+                                           unsigned& low) {
   a *= s;
   b *= s;
   const f16x2 hv = __builtin_convertvector((f32x2v){a, b}, f16x2);
   const float ra = 2048.f * (a - (float)hv.x), rb = 2048.f * (b - (float)hv.y);
   h = __builtin_bit_cast(unsigned, hv);
   l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2v){ra, rb}, f16x2));
+  if constexpr (Count) count_pair(a, b, h, top, low);
 }
-// Power-of-two scale that brings a value of magnitude m to [1, 2), as its exponent field.  The lower the
-// target, the more growth fits (2^15 here) and the higher the floor below which bits are lost (2^-36 of m).
-// Short bonds make some rows far larger than the first 32 of a chunk, and a tile that overflows
-// costs a second, fp32 pass: target 2^6 (growth 2^9) 370 ms for a step of 32 mixed structures, 2^2 334, 1 325,
-// 2^-3 323; small batch 14.1, 13.4, 13.4 and 13.3 ms.
-__device__ __forceinline__ int scale_field(float m) {
-  const int f = 254 - (int)(__float_as_uint(m) >> 23);
-  return f < 1 ? 1 : f;
+// h alone, counted.
+__device__ __forceinline__ unsigned split_high(float a, float b, float s, float& top, unsigned& low) {
+  a *= s;
+  b *= s;
+  const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2v){a, b}, f16x2));
+  count_pair(a, b, h, top, low);
+  return h;
+}
+// Power-of-two scale that brings a value of magnitude m to [2^target, 2^(target + 1)), as its exponent field.  The
+// lower the target, the more growth fits (up to 2^(16 - target)) and the higher the floor below which bits are
+// lost (2^-(36 + target) of m).
+// Weight gradients, target 0: short bonds make some rows far larger than the first 32 of a chunk, and a tile
+// that overflows costs a second, fp32 pass.  Step of 32 mixed structures with target 2^6 370 ms, 2^2 334, 1 325, 2^-3
+// 323; small batch 14.1, 13.4, 13.4 and 13.3 ms.
+// Row products contract over features, which differ less: fewer than one tile in 10^4 of the training steps
+// measured below outgrows target 2^8, and it makes 2^16, the largest magnitude that fp16 holds, a bound of
+// every value that is close enough for one comparison per tile (LowCount).  With target 1 the largest value of the
+// tile has to be kept instead: product of 150 001 rows, K = 512, N = 2048 1359 us against 1272.
+constexpr int kRowsTarget = 8;
+__device__ __forceinline__ int scale_field(float m, int target) {
+  const int f = 254 + target - (int)(__float_as_uint(m) >> 23);
+  return f < 1 ? 1 : f > 254 ? 254 : f;
 }
 
 // Buffer loads of the staged operands: 32-bit offsets from the tile's (uniform) base, zero past `bytes`.
@@ -569,10 +596,94 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float* p, long
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x00027000);
 }
 
+// What the split may lose at the low end, and whether that matters.  A scaled value x is off by at most
+// 2^-23 |x| + w(x) 2^-36, w = max(0, 1 - 2^13 |x|): half a unit of the smallest l.  The product l l' that
+// is left out adds at most as much again.  With low(i) the sum of w over row i (column j) and top(i) its
+// largest |x|, entry (i, j) is off by less than 2^-35 (low(i) top(j) + low(j) top(i)) beyond what full
+// splits leave.  That is harmless up to 2^-21 sum |a b|, the size of eight roundings; a tile where it may
+// be more is taken on the fp32 instructions.  Lower bounds of sum |a b| are sums of h h' of the magnitudes
+// over some of the k, one after the other:
+//  * the last one or two stages, whose planes are in LDS anyway.  Row products compare the tile's smallest
+//    entry with low <= K and top <= 2^16.  In weight gradients magnitudes differ much more along the
+//    contraction: they count low and top of every column as they convert, and compare entry by entry.
+//  * four stages spread over K, weight gradients 16 also.
+//  * all stages, entry by entry.
+// In a step of 32 mixed structures at d = 512 the first clears 99.95 % of the row products' tiles (the rest have rows
+// of zeros) and 52 % of the weight gradients', four stages 42 %, 16 stages 4.0 %, all 1.1 %; 0.1 % lose too much, and
+// 0.3 % have overflowed.  In the small batch the first clears all and 93 %.  What it costs: that product
+// 1294 -> 1321 us, weight gradient 330 011 x 128 x 512 262 -> 278 (half of it the counting), step of 32 mixed structures 330 -> 346 ms,
+// small batch 13.2 -> 13.7.  Counting in row products as well: 1262 -> 1358 us.
+struct LowCount {   // low and top of the tile's rows [0, 128) and columns [128, 256), in LDS
+  unsigned* low;   // in 2048ths while they are added up; share() makes them floats, low / 2^14
+  float* top;
+  __device__ __forceinline__ explicit LowCount(float* smem)
+      : low(reinterpret_cast<unsigned*>(smem + SMEM_BODY + GBM + GBN)), top(smem + SMEM_BODY + 2 * (GBM + GBN)) {}
+  __device__ __forceinline__ void add(int p, unsigned l, float t) const {   // t >= 0: ordered like its bits
+    atomicAdd(low + p, l);
+    atomicMax(reinterpret_cast<unsigned*>(top + p), __float_as_uint(t));
+  }
+  // 2^-35 / 2^-21 of the counts; a row of zeros loses nothing
+  __device__ __forceinline__ void share(int p) const {
+    low[p] = __float_as_uint(top[p] > 0.f ? 1.f / 2048.f / 16384.f * (float)low[p] : 0.f);
+  }
+  __device__ __forceinline__ const float* shares() const { return reinterpret_cast<const float*>(low); }
+};
+// Whether every entry of m (this wave's sums of magnitudes) reaches its bound.
+template <int BI>
+__device__ __forceinline__ bool covered(const LowCount& c, int wm, int wn, int lr, int hf, const f32x16 (&m)[BI][2]) {
+  float miss = 0.f, lc[2], tc[2];
+#pragma unroll
+  for (int bj = 0; bj < 2; ++bj) {
+    const int p = GBM + wn * 64 + bj * 32 + lr;
+    tc[bj] = c.top[p];
+    lc[bj] = c.shares()[p];
+  }
+#pragma unroll
+  for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const int p = wm * 32 * BI + bi * 32 + 8 * v4 + 4 * hf;
+      const float4 l4 = ld4(c.shares() + p), t4 = ld4(c.top + p);
+      const float l[4] = {l4.x, l4.y, l4.z, l4.w};
+      const float t[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+          miss = fmaxf(miss, fmaf(l[v], tc[bj], fmaf(lc[bj], t[v], -m[bi][bj][4 * v4 + v])));
+    }
+  return !__any(miss > 0.f);
+}
+// The smallest entry of the wave's m, in lane 63.
+template <int BI>
+__device__ __forceinline__ float smallest(const f32x16 (&m)[BI][2]) {
+  float x = m[0][0][0];
+#pragma unroll
+  for (int i = 0; i < BI; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x = fminf(x, m[i][j][v]);
+  auto step = [&](auto ctrl, auto rows) {
+    const int y = __float_as_int(x);
+    x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(y, y, decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+  };
+  using std::integral_constant;
+  const integral_constant<int, 0xf> all;
+  step(integral_constant<int, 0x111>(), all);   // row_shr 1, 2, 4, 8
+  step(integral_constant<int, 0x112>(), all);
+  step(integral_constant<int, 0x114>(), all);
+  step(integral_constant<int, 0x118>(), all);
+  step(integral_constant<int, 0x142>(), integral_constant<int, 0xa>());   // row_bcast 15, 31
+  step(integral_constant<int, 0x143>(), integral_constant<int, 0xc>());
+  return x;
+}
+
 // One operand's stage registers.  load() issues the global loads of stage k; values() gives the
 // operand values of the stage loaded last; publish() and scales() choose the scales from the first stage's
 // values (a barrier lies between them) and store the exponents that undo them, ex[position]; store()
-// writes the planes.
+// writes the planes.  top: the largest |x| of the thread's values, of each column with Count, which also
+// counts low.  store_high() writes the plane of h alone, counted; publish_counts() adds the counts up.
 //
 // Operand stored k-contiguous: thread q takes k-quad q % 8 of rows q / 8 + 32 i, so that eight
 // lanes read one row's 128 bytes.  Rows past the end read the last one (their products are never stored).
@@ -581,6 +692,7 @@ template <class L, int R = 4>
 struct SplitMK {
   static constexpr int kPieces = R;
   static constexpr bool kPaired = false;   // position of row m in the tile: m
+  static constexpr bool kCount = false;
   using Values = float4[R];
   const L& ld;
   __amdgpu_buffer_rsrc_t rs;
@@ -612,7 +724,7 @@ struct SplitMK {
       float m = fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
 #pragma unroll
       for (int o = 1; o < 8; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-      const int f = scale_field(m);
+      const int f = scale_field(m, kRowsTarget);
       s[i] = __uint_as_float((unsigned)f << 23);
       if ((tid & 7) == 0) ex[(tid >> 3) + 32 * i] = 127 - f;
     }
@@ -621,9 +733,10 @@ struct SplitMK {
   __device__ __forceinline__ void store(int i, float4 x, char* d, int tid) const {
     const int kq = tid & 7;
     d += (kq >> 1) * SP_OCT + ((tid >> 3) + 32 * i) * 16 + (kq & 1) * 8;
-    unsigned h[2], l[2];
-    split_pair(x.x, x.y, s[i], h[0], l[0]);
-    split_pair(x.z, x.w, s[i], h[1], l[1]);
+    unsigned h[2], l[2], low;
+    float top;
+    split_pair<false>(x.x, x.y, s[i], h[0], l[0], top, low);
+    split_pair<false>(x.z, x.w, s[i], h[1], l[1], top, low);
     *reinterpret_cast<uint2*>(d) = make_uint2(h[0], h[1]);
     *reinterpret_cast<uint2*>(d + SP_PLANE) = make_uint2(l[0], l[1]);
   }
@@ -635,15 +748,33 @@ struct SplitMK {
 #pragma unroll
     for (int i = 0; i < R; ++i) store(i, x[i], d, tid);
   }
+  struct Counts {
+    unsigned low[R] = {};
+    float top[R] = {};
+  };
+  __device__ __forceinline__ void store_high(const Values& x, int, Counts& c, char* d, int tid) const {
+    const int kq = tid & 7;
+    d += (kq >> 1) * SP_OCT + (tid >> 3) * 16 + (kq & 1) * 8;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      *reinterpret_cast<uint2*>(d + 32 * 16 * i) = make_uint2(split_high(x[i].x, x[i].y, s[i], c.top[i], c.low[i]),
+                                                              split_high(x[i].z, x[i].w, s[i], c.top[i], c.low[i]));
+  }
+  __device__ __forceinline__ static void publish_counts(const Counts& c, const LowCount& to, int p0, int tid) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) to.add(p0 + (tid >> 3) + 32 * i, c.low[i], c.top[i]);
+  }
 };
 
 // Operand stored row-contiguous ([k][m]): wave w takes the eight k-rows of octet w and lane q its
 // columns 2 q and 2 q + 1, so that a load reads a whole 512-byte row of the tile.  Even columns of a
 // 64-column half go to its first 32 positions, odd ones to the last (each lane's store is then next
 // to its neighbour's).  k-rows past the end are zeros; columns past m_end read the last pair.
-template <class L>
+// Count: low and top of every column are kept.
+template <class L, bool Count = false>
 struct SplitKM {
   static constexpr bool kPaired = true;
+  static constexpr bool kCount = Count;
   static constexpr int kPieces = 4;
   using Values = float2[8];
   const L& ld;
@@ -651,7 +782,8 @@ struct SplitKM {
   int vo, mc, kb, ke;
   unsigned h[4], l[4];
   float2 raw[8];
-  float s[2];
+  float s[2], top[2] = {0.f, 0.f};
+  unsigned low[2] = {0, 0};
   __device__ __forceinline__ static int pos(int lane, int j) { return ((lane & 32) << 1) | (j << 5) | (lane & 31); }
   __device__ __forceinline__ static int octet(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
   __device__ __forceinline__ SplitKM(const L& l, int m0, int m_end, int kb_, int ke_, int tid)
@@ -700,7 +832,7 @@ struct SplitKM {
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int f = scale_field(m[j]);
+      const int f = scale_field(m[j], Count ? 0 : kRowsTarget);
       s[j] = __uint_as_float((unsigned)f << 23);
       if (tid < 64) ex[pos(lane, j)] = 127 - f;
     }
@@ -716,7 +848,7 @@ struct SplitKM {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const float2 u = value(i0 + 2 * i, k, tid), v = value(i0 + 2 * i + 1, k, tid);
-      split_pair(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i0 / 2 + i], l[i0 / 2 + i]);
+      split_pair<Count>(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i0 / 2 + i], l[i0 / 2 + i], top[j], low[j]);
     }
     if (n & 1) put(j, d, tid);
     if (j) load_rows(next, i0, 4);
@@ -727,10 +859,46 @@ struct SplitKM {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float2 u = x[2 * i], v = x[2 * i + 1];
-        split_pair(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i], l[i]);
+        split_pair<Count>(j ? u.y : u.x, j ? v.y : v.x, s[j], h[i], l[i], top[j], low[j]);
       }
       put(j, d, tid);
     }
+  }
+  struct Counts {
+    unsigned low[2] = {};
+    float top[2] = {};
+  };
+  __device__ __forceinline__ unsigned past(int k, int tid) const {   // 2048ths that a stage's zeros past the end count
+    const int n = k + 8 * octet(tid) + 8 - ke;
+    return 2048 * (n < 0 ? 0 : n < 8 ? n : 8);
+  }
+  // what the loop has counted
+  __device__ __forceinline__ Counts counts(int last, int tid) const {
+    Counts c;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      c.low[j] = low[j] - past(last, tid);
+      c.top[j] = top[j];
+    }
+    return c;
+  }
+  __device__ __forceinline__ void store_high(const Values& x, int k, Counts& c, char* d, int tid) const {
+    d += octet(tid) * SP_OCT;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      unsigned u[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float2 a = x[2 * i], b = x[2 * i + 1];
+        u[i] = split_high(j ? a.y : a.x, j ? b.y : b.x, s[j], c.top[j], c.low[j]);
+      }
+      c.low[j] -= past(k, tid);
+      *reinterpret_cast<uint4*>(d + pos(tid & 63, j) * 16) = make_uint4(u[0], u[1], u[2], u[3]);
+    }
+  }
+  __device__ __forceinline__ static void publish_counts(const Counts& c, const LowCount& to, int p0, int tid) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) to.add(p0 + pos(tid & 63, j), c.low[j], c.top[j]);
   }
 };
 
@@ -765,17 +933,108 @@ __device__ __forceinline__ void split_stage(const char* st, int wm, int wn, int 
   }
 }
 
+// One stage of sum h h' of the operands' magnitudes.
+template <int BI>
+__device__ __forceinline__ void magnitude_stage(const char* st, int wm, int wn, int lr, int hf, f32x16 (&m)[BI][2]) {
+  auto octet = [&](const char* o, int row) {
+    uint4 x = *reinterpret_cast<const uint4*>(o + row * 16);
+    x.x &= 0x7fff7fffu;
+    x.y &= 0x7fff7fffu;
+    x.z &= 0x7fff7fffu;
+    x.w &= 0x7fff7fffu;
+    return __builtin_bit_cast(f16x8, x);
+  };
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const char* o = st + (2 * g + hf) * SP_OCT;
+    f16x8 a[BI], b[2];
+#pragma unroll
+    for (int c = 0; c < BI; ++c) a[c] = octet(o, wm * 32 * BI + c * 32 + lr);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) b[c] = octet(o + SP_OPER, wn * 64 + c * 32 + lr);
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) m[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], m[i][j], 0, 0, 0);
+  }
+}
+
+// Whether a tile has lost nothing that matters, where its last stages do not show it.  kCount: its counts are
+// complete and m holds the magnitudes of the last two stages; else most is K (top of all rows + top of all columns) / 2^14.
+// The registers hold the operands' first stage.
+template <int BI, class SA, class SB>
+__device__ __forceinline__ bool enough(float* smem, SA& sa, SB& sb, float most, int kb, int ke, int wm, int wn, int lr,
+                                       int hf, int tid, f32x16 (&m)[BI][2]) {
+  constexpr bool kCount = SA::kCount && SB::kCount;
+  char* st = reinterpret_cast<char*>(smem);
+  float* flag = smem + SMEM_BODY + 3 * (GBM + GBN);
+  const LowCount count(smem);
+  auto all = [&](int f, bool ok) {
+    if ((tid & 63) == 63) flag[f + (tid >> 6)] = ok ? 0.f : 1.f;
+    __syncthreads();
+    return flag[f] + flag[f + 1] + flag[f + 2] + flag[f + 3] == 0.f;
+  };
+  // The order of the stages: of 6 or more first a sample (every n / 4-th; with kCount, of 18 or more, then
+  // every n / 16-th between them; none of the last two), then all from the beginning.
+  const int n = (ke - kb + SBK - 1) / SBK, sample = n < 6 ? 0 : kCount && n >= 18 ? 16 : 4;
+  auto at = [&](int q) {
+    if (q >= sample) return q - sample;
+    return (n - 2) * (q < 4 ? 4 * q : q - 3 + (q - 4) / 3) / 16;
+  };
+  for (int q = 0, f = 4, i = 0;; ++q) {
+    if (q == sample || (q == 0 && !kCount)) zero_acc(m);
+    const bool last = q == sample + n - 1;
+    {   // the stage's loads have been issued; issue the next one's
+      typename SA::Values xa;
+      typename SB::Values xb;
+      typename SA::Counts ca;
+      typename SB::Counts cb;
+      sa.values(kb + i * SBK, tid, xa);
+      sa.store_high(xa, kb + i * SBK, ca, st, tid);
+      sb.values(kb + i * SBK, tid, xb);
+      sb.store_high(xb, kb + i * SBK, cb, st + SP_OPER, tid);
+      if (!kCount && q >= sample) {
+        SA::publish_counts(ca, count, 0, tid);
+        SB::publish_counts(cb, count, GBM, tid);
+      }
+      i = last ? 0 : at(q + 1);
+      sa.load(kb + i * SBK);
+      sb.load(kb + i * SBK);
+    }
+    __syncthreads();
+    magnitude_stage<BI>(st, wm, wn, lr, hf, m);
+    __syncthreads();
+    if constexpr (kCount) {
+      if (last || (q == 3 && sample) || (q == 15 && sample == 16)) {
+        if (all(f, covered<BI>(count, wm, wn, lr, hf, m))) return true;
+        if (last) return false;
+        f += 4;
+      }
+    } else {
+      if (last) break;
+      if (sample && q == 3 && all(4, smallest<BI>(m) >= most)) return true;
+    }
+  }
+  count.share(tid);
+  __syncthreads();
+  return all(8, covered<BI>(count, wm, wn, lr, hf, m));
+}
+
 // The K loop of the split products over [kb, ke).  A and B: loader, first and last row (column)
 // of the tile's operand.  On return hi holds h h' + 2^-11 (h l' + l h') of the scaled operands and
-// smem the exponents that undo the scales; false if a value is not finite.
+// smem the exponents that undo the scales; false if a value is not finite or the split may have lost too much.
 template <class SA, class SB, int BI, class LA, class LB>
 __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, int a1, const LB& bl, int b0, int b1,
                                            int kb, int ke, int wm, int wn, int lr, int hf, int tid,
                                            f32x16 (&hi)[BI][2]) {
   char* lds = reinterpret_cast<char*>(smem);
   int* ex = reinterpret_cast<int*>(smem + SMEM_BODY);   // [128] rows, [128] columns
-  float* flag = smem + SMEM_BODY + GBM + GBN;
+  float* flag = smem + SMEM_BODY + 3 * (GBM + GBN);   // [4] each, one of a wave
+  const LowCount count(smem);
+  count.low[tid] = 0;
+  count.top[tid] = 0.f;
   f32x16 lo[BI][2];
+  constexpr bool kCount = SA::kCount && SB::kCount;
   zero_acc(hi);
   zero_acc(lo);
   SA sa(al, a0, a1, kb, ke, tid);
@@ -802,21 +1061,32 @@ __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, in
   int k1 = kb + SBK < last ? kb + SBK : last;
   sa.load(k1);
   sb.load(k1);
+  auto publish_counts = [&]() {   // every value has been split
+    if constexpr (kCount) {
+      SA::publish_counts(sa.counts(last, tid), count, 0, tid);
+      SB::publish_counts(sb.counts(last, tid), count, GBM, tid);
+    }
+  };
+  if (kCount && kb == last) {
+    __syncthreads();   // the counts are zero
+    publish_counts();
+  }
   __syncthreads();
   int cur = 0;
   for (int k = kb; k < last; k += SBK) {
     char* d = lds + (cur ^ 1) * SP_STAGE;
-    const int next = k1 + SBK < last ? k1 + SBK : last;
+    const int next = k1 < last ? k1 + SBK : kb;   // the first stage again for enough()
     split_stage<BI, SA::kPieces + SB::kPieces>(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [&](int n) {
       if (n < SA::kPieces) sa.piece(n, k1, next, d, tid); else sb.piece(n - SA::kPieces, k1, next, d + SP_OPER, tid);
       __builtin_amdgcn_sched_barrier(0);   // keeps the parts where they are
     });
+    if (k1 == last) publish_counts();
     k1 = next;
     __syncthreads();
     cur ^= 1;
   }
+  if constexpr (kCount) count.share(tid);
   split_stage<BI, 1>(lds + cur * SP_STAGE, wm, wn, lr, hf, hi, lo, [](int) {});
-  __syncthreads();
   float z = 0.f;
 #pragma unroll
   for (int i = 0; i < BI; ++i)
@@ -827,10 +1097,29 @@ __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, in
         hi[i][j][v] = fmaf(lo[i][j][v], 1.f / 2048.f, hi[i][j][v]);
         z = fmaf(hi[i][j][v], 0.f, z);   // not a number once a value is infinite or not a number
       }
-  const bool bad = __any(z != z);
-  if ((tid & 63) == 0) flag[tid >> 6] = bad ? 1.f : 0.f;
+  auto put = [&](int f, float x) {
+    if ((tid & 63) == 63) flag[f + (tid >> 6)] = x;
+  };
+  put(0, __any(z != z) ? 1.f : 0.f);
+  // the magnitudes of the last stage, and of the one before it, whose planes are still there
+  zero_acc(lo);
+  magnitude_stage<BI>(lds + cur * SP_STAGE, wm, wn, lr, hf, lo);
+  if (last >= kb + (kCount ? 7 : 31) * SBK) magnitude_stage<BI>(lds + (cur ^ 1) * SP_STAGE, wm, wn, lr, hf, lo);
+  if constexpr (!kCount) {
+    put(4, smallest<BI>(lo));
+  }
   __syncthreads();
-  return flag[0] + flag[1] + flag[2] + flag[3] == 0.f;
+  if (flag[0] + flag[1] + flag[2] + flag[3] != 0.f) return false;
+  const float most = 8.f * (float)(ke - kb);
+  if constexpr (kCount) {
+    put(4, covered<BI>(count, wm, wn, lr, hf, lo) ? 0.f : 1.f);
+    __syncthreads();
+    if (flag[4] + flag[5] + flag[6] + flag[7] == 0.f) return true;
+  } else {
+    if (fminf(fminf(flag[4], flag[5]), fminf(flag[6], flag[7])) >= most) return true;
+  }
+  __syncthreads();   // the flags are written again
+  return enough<BI>(smem, sa, sb, most, kb, ke, wm, wn, lr, hf, tid, lo);
 }
 
 // Undo the scales: acc[bi][bj][v] is row 32 bi + 8 (v / 4) + 4 hf + v % 4, column 32 bj + lr of the wave.
@@ -1092,7 +1381,7 @@ template <class ALoad, class BLoad>
 __device__ __forceinline__ bool wgrad_split(float* smem, const ALoad& al, const BLoad& bl, int P, int Q,
                                             const WChunk& ch, int p0, int q0, int wm, int wn, int lr, int hf, int tid,
                                             f32x16 (&acc)[2][2]) {
-  if (!split_loop<SplitKM<ALoad>, SplitKM<BLoad>, 2>(smem, al, p0, P, bl, q0, Q, ch.r0, ch.r1, wm, wn, lr, hf, tid, acc))
+  if (!split_loop<SplitKM<ALoad, true>, SplitKM<BLoad, true>, 2>(smem, al, p0, P, bl, q0, Q, ch.r0, ch.r1, wm, wn, lr, hf, tid, acc))
     return false;
   unscale<2>(smem, wm, wn, lr, hf, acc);
   return true;

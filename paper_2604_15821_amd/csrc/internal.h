@@ -162,10 +162,10 @@ using Fp32Only = std::false_type;
 constexpr Fp32Only kFp32{};
 
 // What the split products take: whole stages of K, and operand tiles within the 32-bit offsets
-// of buffer loads (the tile's first row to its last, and one stage past it).  Anything else is
-// multiplied on the fp32 instructions.
+// of buffer loads (the tile's first row to its last, and one stage past it), and K within the 32 bits of
+// a row's low count (2048 K).  Anything else is multiplied on the fp32 instructions.
 inline bool split_takes_rows(int K, int N) {
-  return K % SBK == 0 && 4LL * K * GBM <= INT32_MAX && 4LL * (K + 2 * SBK) * N <= INT32_MAX;
+  return K % SBK == 0 && K <= 1 << 20 && 4LL * K * GBM <= INT32_MAX && 4LL * (K + 2 * SBK) * N <= INT32_MAX;
 }
 inline bool split_takes_wgrad(int P, int Q) {   // chunks are at most 2048 rows
   return 4LL * (2048 + 2 * SBK) * (P > Q ? P : Q) <= INT32_MAX;

@@ -1,11 +1,12 @@
 """Operands of one training step that the split products hold only in part, where the loader
-transforms them (SiLU' of the readout): against the float64 oracle, within the tolerances of the step."""
+transforms them (SiLU of pre-activations, SiLU' of the readout): against the float64 oracle, every
+tensor and every column of it within the tolerances of the step."""
 import copy
 
 import numpy as np
 import pytest
 
-from helpers import TOL_W, banner, rel_l2
+from helpers import TOL_E, TOL_F, TOL_LOSS, TOL_W, banner, energy_error, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +38,19 @@ def _forward(b):
     return forward_energy(b.species, g, P, route_all(b.species, g, P))[1]
 
 
+def _compare(b):
+    from oracle.model import training_step
+    loss, E, F, grad = training_step(b)
+    l1, E1, F1, g1 = _step(b)
+    assert abs(l1 - loss) <= TOL_LOSS * abs(loss)
+    assert energy_error(E1, E, _forward(b)["eps"], b.offsets) <= TOL_E
+    assert rel_l2(F1, F) <= TOL_F
+    for k, ref in grad.items():
+        if np.linalg.norm(ref) > 0:
+            assert rel_l2(g1[k], ref) <= TOL_W, k
+    return grad, g1
+
+
 def test_readout_column_far_below_the_padding_of_its_chunk():
     """dW_o1 of one 32-atom cell cut to 20 atoms: a chunk shorter than one stage, whose padded rows must not
     set the scale of a column with SiLU'(z) = -3e-12 in every atom."""
@@ -55,3 +69,28 @@ def test_readout_column_far_below_the_padding_of_its_chunk():
     dz = 64 * 2.0 ** -24 * (np.abs(h) @ np.abs(b.weights["W_o1"][:, 7])).max()
     assert dz < 1e-3
     assert rel_l2(got, ref) <= TOL_W + dz
+
+
+@pytest.mark.parametrize("e", [16, 24, 34])
+def test_hidden_units_without_weight_set_the_scale(e):
+    """31 hidden units 2^e times as large as the others, with rows of zeros in the second layer: all of
+    the result comes from values 2^e below their row's scale."""
+    banner("split step, hidden units without weight", e)
+    b = _batch(2)
+    for t in range(b.model.n_blocks):
+        b.weights[f"blocks.{t}.W1"][:, :, :31] *= np.float32(2.0 ** e)
+        b.weights[f"blocks.{t}.W2"][:, :31, :] = 0.0
+    grad, got = _compare(b)
+    for t in range(b.model.n_blocks):   # the others' gradients on their own
+        assert rel_l2(got[f"blocks.{t}.W2"][:, 31:], grad[f"blocks.{t}.W2"][:, 31:]) <= TOL_W
+        assert rel_l2(got[f"blocks.{t}.W1"][:, :, 31:], grad[f"blocks.{t}.W1"][:, :, 31:]) <= TOL_W
+
+
+def test_hidden_units_that_outgrow_the_scale():
+    """The first 32 hidden units 2^-17 of the others' size: tiles that overflow the scale go through the
+    fp32 pass with the SiLU loaders."""
+    banner("split step, growing hidden units")
+    b = _batch(2)
+    for t in range(b.model.n_blocks):
+        b.weights[f"blocks.{t}.W1"][:, :, :32] *= np.float32(2.0 ** -17)
+    _compare(b)
