@@ -247,8 +247,8 @@ extern "C" int janus_grouped_gemm_noalloc(const float* A, const float* B, float*
   RowsTile* tiles = cv.take<RowsTile>(mt);
   int* nt = cv.take<int>(1);
   if (cv.size() > kNoAllocScratchBytes) return JANUS_ENOMEM;
-  // the table kernel rewrites the count and every tile the launch reads, so
-  // nothing left by an earlier call is used
+  // the table kernel rewrites the count and every tile that the launch reads (a launch
+  // without a table reads neither), so nothing left by an earlier call is used
   grouped_rows(st, A, B, C, row_off, n_groups, K, N, trans_b, tiles, nt, mt);
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;

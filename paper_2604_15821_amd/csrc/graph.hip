@@ -428,59 +428,53 @@ __device__ __forceinline__ long long block_exclusive_scan(long long v, long long
   return r;
 }
 
-// The same by one workgroup, for inputs of up to kScanOne values: one launch in place of three, each
-// of which takes 3 to 5 us whatever its size.  The line lies at one round of the workgroup: with two
-// the chain of rounds costs more than it saves (whole neighbour list of 32 262 atoms 208.5 us, 202.3
-// by three launches).
-constexpr int kScanOneThreads = 1024, kScanOne = 16384;
+// The same by one workgroup, for inputs of up to kScanOne values, kScanOnePer to a thread: one launch in
+// place of three, each of which takes 3 to 5 us whatever its size.  Longer inputs would take a loop, and
+// its chain of rounds costs more than it saves (two rounds: whole neighbour list of 32 262 atoms 208.5 us,
+// 202.3 by three launches).
+constexpr int kScanOneThreads = 1024, kScanOnePer = 16, kScanOne = kScanOneThreads * kScanOnePer;
 __global__ __launch_bounds__(kScanOneThreads) void scan_one_kernel(const int* __restrict__ in, int n,
                                                                    int* __restrict__ out, int* __restrict__ flag) {
   __shared__ long long wsum[kScanOneThreads / 64];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  long long carry = 0;
-  constexpr int kPer = 16;
-  for (int i0 = 0; i0 < n; i0 += kPer * kScanOneThreads) {
-    const int i = i0 + kPer * t;
-    int v[kPer];
-    long long s = 0;
-    if (i + kPer <= n) {
+  const int i = kScanOnePer * t;
+  int v[kScanOnePer];
+  long long s = 0;
+  if (i + kScanOnePer <= n) {
 #pragma unroll
-      for (int k = 0; k < kPer; k += 4) {
-        const int4 u = *reinterpret_cast<const int4*>(in + i + k);
-        v[k] = u.x; v[k + 1] = u.y; v[k + 2] = u.z; v[k + 3] = u.w;
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) v[k] = i + k < n ? in[i + k] : 0;
+    for (int k = 0; k < kScanOnePer; k += 4) {
+      const int4 u = *reinterpret_cast<const int4*>(in + i + k);
+      v[k] = u.x; v[k + 1] = u.y; v[k + 2] = u.z; v[k + 3] = u.w;
     }
+  } else {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) s += v[k];
-    long long inc = s;   // inclusive scan over the wave
+    for (int k = 0; k < kScanOnePer; ++k) v[k] = i + k < n ? in[i + k] : 0;
+  }
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const long long u = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += u;
-    }
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    long long before = carry, total = 0;
+  for (int k = 0; k < kScanOnePer; ++k) s += v[k];
+  long long inc = s;   // inclusive scan over the wave
 #pragma unroll
-    for (int q = 0; q < kScanOneThreads / 64; ++q) {
-      if (q < w) before += wsum[q];
-      total += wsum[q];
-    }
-    long long run = before + inc - s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long u = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += u;
+  }
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  long long before = 0, total = 0;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      if (i + k < n) out[i + k] = (int)run;
-      run += v[k];
-    }
-    carry += total;
-    __syncthreads();
+  for (int q = 0; q < kScanOneThreads / 64; ++q) {
+    if (q < w) before += wsum[q];
+    total += wsum[q];
+  }
+  long long run = before + inc - s;
+#pragma unroll
+  for (int k = 0; k < kScanOnePer; ++k) {
+    if (i + k < n) out[i + k] = (int)run;
+    run += v[k];
   }
   if (t == 0) {
-    out[n] = (int)carry;
-    if (carry > 0x7fffffffLL && flag) atomicOr(flag, 16);
+    out[n] = (int)total;
+    if (total > 0x7fffffffLL && flag) atomicOr(flag, 16);
   }
 }
 
@@ -538,11 +532,12 @@ __global__ void scan_tile_kernel(const int* __restrict__ in, int n, const long l
 
 // rev[e] = the edge (j, i, -n), found by binary search in the sorted segment of j.  Bound by the
 // scattered loads of the search, so only one edge of a pair searches (i < j, or i = j and the first
-// non-zero shift positive) and writes both entries; the write pass has left rev[e] = e, which an edge
-// without a partner keeps (flag bit 8).  2.1 M edges: 87 us with every edge searching, now 55.
+// non-zero shift positive) and writes both entries: 2.1 M edges 87 us with every edge searching, now 55.
+// Every edge has its partner, because the distance test gives the same value both ways (differences and
+// shifts only change sign, exactly); the write pass has set rev[e] = e, so that nothing is left unwritten.
 __global__ void reverse_kernel(const int* __restrict__ ei, const int* __restrict__ ej,
                                const int8_t* __restrict__ shift, const int* __restrict__ rowptr, int Ne,
-                               int* __restrict__ rev, int* __restrict__ flag) {
+                               int* __restrict__ rev) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= Ne) return;
   const int i = ei[e], j = ej[e];
@@ -569,8 +564,6 @@ __global__ void reverse_kernel(const int* __restrict__ ei, const int* __restrict
   if (ok) {
     rev[e] = lo;
     rev[lo] = e;
-  } else {
-    atomicOr(flag, 8);
   }
 }
 
@@ -822,8 +815,7 @@ extern "C" int janus_build_edges(janus_ctx* ctx, const float* pos, const float* 
                          bstart, batoms, count, rp, ei, ej, shift, rev);
     hipLaunchKernelGGL((nl_kernel<true>), gw, b256, 0, st, pos, cell, offsets, sid, r_cut, N, count, rp, ei, ej,
                        shift, rev, grid);
-    hipLaunchKernelGGL(reverse_kernel, dim3(cdiv(ne, 256)), dim3(256), 0, st, ei, ej, shift, rp, (int)ne, rev,
-                       flag);
+    hipLaunchKernelGGL(reverse_kernel, dim3(cdiv(ne, 256)), dim3(256), 0, st, ei, ej, shift, rp, (int)ne, rev);
   }
   JANUS_HIP_TRY(hipGetLastError());
   return JANUS_OK;
