@@ -296,7 +296,7 @@ int janus_build_edges(janus_ctx* ctx, const float* pos, const float* cell, const
  * reaches (widened far beyond fp32 rounding), with the same fp32 test, and
  * sorts what it keeps into the canonical order, so both give the same list bit
  * for bit.  mode 0 (default): the cell list for a structure with
- * n_s * n_images >= 81920 whose box holds at least 27 bins, all pairs
+ * n_s * n_images >= 65536 whose box holds at least 27 bins, all pairs
  * otherwise; 1: the cell list for every structure; 2: all pairs for every
  * structure.  A centre with more than 512 neighbours is written by the
  * all-pairs kernel in every mode.  Errors: JANUS_EINVAL (ctx null, mode

@@ -21,10 +21,15 @@ __device__ __forceinline__ void image_range(const float* L, float rc, int& mx, i
 }
 
 // All-pairs candidates n_s * n_images from which a structure may use the cell list in mode 0.  The whole
-// build at r_cut = 6 and 27 images, all pairs against cell list: 536 and 865 us for 32 structures of 1200
-// atoms, 1169 and 1425 for 32 of 2048, 248 and 284 for 4 of 2048, 535 and 327 for 2 of 5000; the
-// line lies at 3034 atoms of 27 images.
-constexpr long long kCellMinCand = 81920;
+// build at r_cut = 6 and 0.1 atoms per cubic Angstrom, all pairs against cell list in us, for 1, 4 and 16 cells:
+//   27 images, 2048 atoms (55 296 candidates)  179 177, 264 301, 654 769
+//   27 images, 2500 atoms (67 500)             206 190, 343 332, 887 893
+//   27 images, 3000 atoms (81 000)             232 189, 438 387, 1156 1070
+//   75 images,  600 atoms (45 000)             173 203, 195 234, 357 456
+//   75 images,  900 atoms (67 500)             233 210, 280 264, 644 610
+//   75 images, 1100 atoms (82 500)             270 212, 356 299, 863 709
+// The two meet between 55 000 and 68 000 whatever the number of cells and images.
+constexpr long long kCellMinCand = 65536;
 
 // Flag bits: 1 bad offsets, 2 unsupported cell, 32 (with rc > 0) a structure that may use the cell list.
 __global__ void validate_struct_kernel(const int* __restrict__ offsets, int S, int N, const float* __restrict__ cell,
