@@ -234,6 +234,8 @@ def main():
         "config": {"workload": args.workload, "structures": S, "atoms": N, "edges": Ne, "d": m.d,
                    "d_hidden": m.d_hidden, "experts": m.n_experts, "top_k": m.top_k, "blocks": m.n_blocks,
                    "n_rbf": m.n_rbf, "r_cut": m.r_cut, "parallelism": "none",
+                   "products": "fp32 matrix instructions" if m.n_heads else
+                   "fp32 operands as two fp16 terms, three 16-bit matrix products",
                    "streams": 1 if args.serial else 2,
                    **({"workspace_mib": args.workspace_mib} if args.workspace_mib else {}),
                    **({"atom_moe": {"experts": m.n_experts_f, "top_k": m.top_k_f, "d_hidden": m.d_hidden_f}}

@@ -249,11 +249,11 @@ def trace_summary(workload: str, runs: str, steps: int) -> str:
     return "\n".join(L) + "\n"
 
 
-# Executed fp32 matrix work and matrix-pipe busy cycles per dispatch.  rocprofv3's own
-# derived metrics define MfmaFlopsF32 = 512 SQ_INSTS_VALU_MFMA_MOPS_F32 and MfmaUtil =
+# Executed matrix work and matrix-pipe busy cycles per dispatch.  rocprofv3's own derived
+# metrics define MfmaFlopsF32 (F16) = 512 SQ_INSTS_VALU_MFMA_MOPS_F32 (F16) and MfmaUtil =
 # sum(SQ_VALU_MFMA_BUSY_CYCLES) / (max over XCDs of GRBM_GUI_ACTIVE x 1024 SIMDs); the CSV
 # gives GRBM_GUI_ACTIVE summed over the 8 XCDs, whose max is taken as that sum / 8.
-MFMA_COUNTERS = ("SQ_INSTS_VALU_MFMA_MOPS_F32", "SQ_VALU_MFMA_BUSY_CYCLES", "GRBM_GUI_ACTIVE")
+MFMA_COUNTERS = ("SQ_INSTS_VALU_MFMA_MOPS_F32", "SQ_INSTS_VALU_MFMA_MOPS_F16", "SQ_VALU_MFMA_BUSY_CYCLES", "GRBM_GUI_ACTIVE")
 N_XCD, N_SIMD = 8, 1024
 MFMA_RUN_STEPS = 2   # the counter pass below runs one breakdown step and one timed step
 
@@ -271,8 +271,9 @@ _BENCH_FAMILY = {"expert_gemm": "expert_gemm", "wgrad": "expert_wgrad"}
 
 
 def mfma_summary(workload: str, runs: str) -> str:
-    """Markdown summary of one counter pass: executed fp32 MFMA work against the algorithmic
-    work bench.py counts, matrix-pipe busy fraction and clock, per kernel and per family."""
+    """Markdown summary of one counter pass: executed MFMA work, fp32 and 16-bit (split products),
+    against the algorithmic work bench.py counts, matrix-pipe busy fraction and clock, per kernel and
+    per family."""
     per = collections.defaultdict(lambda: collections.defaultdict(float))
     names, dur = {}, {}
     with open(f"{runs}/tr_m_{workload}/run_counter_collection.csv") as f:
@@ -286,33 +287,37 @@ def mfma_summary(workload: str, runs: str) -> str:
     if os.path.exists(log):
         lines = [x for x in open(log) if x.startswith("{")]
         bench_line = json.loads(lines[-1]) if lines else None
-    kern = collections.defaultdict(lambda: [0, 0.0, 0.0, 0.0, 0.0])   # dispatches, s, flops, busy, gui/8
-    fam = collections.defaultdict(lambda: [0, 0.0])                   # dispatches, executed flops
+    kern = collections.defaultdict(lambda: [0, 0.0, 0.0, 0.0, 0.0, 0.0])   # dispatches, s, flops, busy, gui/8, 16-bit flops
+    fam = collections.defaultdict(lambda: [0, 0.0, 0.0])   # dispatches, executed fp32 and 16-bit flops
     for k, c in per.items():
         n = re.sub(r"\(.*", "", names[k].replace("janus::", ""))
-        flops = 512.0 * c["SQ_INSTS_VALU_MFMA_MOPS_F32"]
+        f32, f16 = (512.0 * c[f"SQ_INSTS_VALU_MFMA_MOPS_{t}"] for t in ("F32", "F16"))
         a = kern[n]
         a[0] += 1
         a[1] += dur[k]
-        a[2] += flops
+        a[2] += f32 + f16
+        a[5] += f16
         a[3] += c["SQ_VALU_MFMA_BUSY_CYCLES"]
         a[4] += c["GRBM_GUI_ACTIVE"] / N_XCD
         f = fam[family(names[k])]
         f[0] += 1
-        f[1] += flops
-    L = [f"# Executed fp32 matrix work, training step, workload `{workload}`", "",
+        f[1] += f32
+        f[2] += f16
+    L = [f"# Executed matrix work, training step, workload `{workload}`", "",
          "Command (run from /tmp on an MI355X with `TMPDIR=/tmp`, repo at `$R`, outputs under `$OUT`):", "",
          "```", mfma_command(workload), "```", "",
          f"Summarised by `python -m paper_2604_15821_amd.counters --mfma {workload} $OUT`. Executed work is "
-         "512 x SQ_INSTS_VALU_MFMA_MOPS_F32 (rocprofv3's MfmaFlopsF32); the matrix-pipe busy fraction is "
+         "512 x SQ_INSTS_VALU_MFMA_MOPS_F32 and _F16 (rocprofv3's MfmaFlopsF32, MfmaFlopsF16); a split product "
+         "takes three 16-bit products and the magnitudes that show what it may lose; the matrix-pipe busy fraction is "
          "SQ_VALU_MFMA_BUSY_CYCLES over (GRBM_GUI_ACTIVE / 8) x 1024 SIMDs (its MfmaUtil; the CSV sums "
          "GRBM_GUI_ACTIVE over the 8 XCDs); the clock is GRBM_GUI_ACTIVE / 8 over the dispatch's duration. "
          "Dispatches run one at a time under the counter pass, so durations are those of each kernel alone.", ""]
     if bench_line:
         L += ["Per family, per training step (the algorithmic work is what bench.py counts for the same run: "
               "2 x rows x K x N per product, no padding):", "",
-              "| family | dispatches per step | executed TFLOP per step | algorithmic TFLOP per step | executed / algorithmic |",
-              "|---|---:|---:|---:|---:|"]
+              "| family | dispatches per step | executed fp32 TFLOP per step | executed 16-bit TFLOP per step | "
+              "algorithmic TFLOP per step | (fp32 + 16-bit / 3) / algorithmic |",
+              "|---|---:|---:|---:|---:|---:|"]
         fams = _BENCH_FAMILY
         if bench_line["config"].get("attention_heads"):
             # the q|k|v and Wo products run on the expert kernels but count as dense in bench.py
@@ -323,16 +328,17 @@ def mfma_summary(workload: str, runs: str) -> str:
                 continue
             steps = MFMA_RUN_STEPS
             alg = kb.get("flops_per_step", kb["tflops"] * kb["ms_per_step"] * 1e9) * 1e-12
-            ex = fam[cf][1] / steps / 1e12
-            L.append(f"| {cf} | {fam[cf][0] / steps:.0f} | {ex:.3f} | {alg:.3f} | {ex / alg:.4f} |")
+            e32, e16 = (x / steps / 1e12 for x in fam[cf][1:])
+            L.append(f"| {cf} | {fam[cf][0] / steps:.0f} | {e32:.3f} | {e16:.3f} | {alg:.3f} | "
+                     f"{(e32 + e16 / 3) / alg:.4f} |")
         L.append("")
-    L += ["| kernel | dispatches | avg us | executed GFLOP per dispatch | TFLOP/s | MFMA busy | clock GHz |",
-          "|---|---:|---:|---:|---:|---:|---:|"]
+    L += ["| kernel | dispatches | avg us | executed GFLOP per dispatch | TFLOP/s | MFMA busy | clock GHz | 16-bit share |",
+          "|---|---:|---:|---:|---:|---:|---:|---:|"]
     for n, a in sorted(kern.items(), key=lambda kv: -kv[1][1]):
         if a[2] <= 0:
             continue
         L.append(f"| `{n}` | {a[0]} | {a[1] / a[0] * 1e6:.1f} | {a[2] / a[0] / 1e9:.2f} | {a[2] / a[1] / 1e12:.1f} | "
-                 f"{a[3] / (a[4] * N_SIMD):.3f} | {a[4] / a[1] / 1e9:.2f} |")
+                 f"{a[3] / (a[4] * N_SIMD):.3f} | {a[4] / a[1] / 1e9:.2f} | {a[5] / a[2]:.4f} |")
     return "\n".join(L) + "\n"
 
 

@@ -682,8 +682,8 @@ __device__ __forceinline__ float smallest(const f32x16 (&m)[BI][2]) {
 // One operand's stage registers.  load() issues the global loads of stage k; values() gives the
 // operand values of the stage loaded last; publish() and scales() choose the scales from the first stage's
 // values (a barrier lies between them) and store the exponents that undo them, ex[position]; store()
-// writes the planes.  top: the largest |x| of the thread's values, of each column with Count, which also
-// counts low.  store_high() writes the plane of h alone, counted; publish_counts() adds the counts up.
+// writes the planes.  With Count low and top of every column are counted on the way (LowCount).
+// store_high() writes the plane of h alone and counts; publish_counts() adds the counts up.
 //
 // Operand stored k-contiguous: thread q takes k-quad q % 8 of rows q / 8 + 32 i, so that eight
 // lanes read one row's 128 bytes.  Rows past the end read the last one (their products are never stored).
@@ -959,9 +959,9 @@ __device__ __forceinline__ void magnitude_stage(const char* st, int wm, int wn, 
   }
 }
 
-// Whether a tile has lost nothing that matters, where its last stages do not show it.  kCount: its counts are
-// complete and m holds the magnitudes of the last two stages; else most is K (top of all rows + top of all columns) / 2^14.
-// The registers hold the operands' first stage.
+// Whether a tile has lost nothing that matters, where its last stages do not show it.  m holds their magnitudes;
+// kCount: the tile's counts are complete; else every entry of m from `most` on is enough.  The registers hold
+// the operands' first stage.
 template <int BI, class SA, class SB>
 __device__ __forceinline__ bool enough(float* smem, SA& sa, SB& sb, float most, int kb, int ke, int wm, int wn, int lr,
                                        int hf, int tid, f32x16 (&m)[BI][2]) {
@@ -1105,12 +1105,10 @@ __device__ __forceinline__ bool split_loop(float* smem, const LA& al, int a0, in
   zero_acc(lo);
   magnitude_stage<BI>(lds + cur * SP_STAGE, wm, wn, lr, hf, lo);
   if (last >= kb + (kCount ? 7 : 31) * SBK) magnitude_stage<BI>(lds + (cur ^ 1) * SP_STAGE, wm, wn, lr, hf, lo);
-  if constexpr (!kCount) {
-    put(4, smallest<BI>(lo));
-  }
+  if constexpr (!kCount) put(4, smallest<BI>(lo));
   __syncthreads();
   if (flag[0] + flag[1] + flag[2] + flag[3] != 0.f) return false;
-  const float most = 8.f * (float)(ke - kb);
+  const float most = 8.f * (float)(ke - kb);   // K (2^16 + 2^16) 2^-35 / 2^-21
   if constexpr (kCount) {
     put(4, covered<BI>(count, wm, wn, lr, hf, lo) ? 0.f : 1.f);
     __syncthreads();
