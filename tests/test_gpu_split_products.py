@@ -211,3 +211,53 @@ def test_infinities_and_nan_stay_in_their_rows_and_columns(ctx, bad, rows):
     assert (got[np.isinf(ref32)] == ref32[np.isinf(ref32)]).all()
     bound = 104 * 2.0 ** -24 * (np.abs(A[:, :]).astype(np.float64) @ np.abs(B[0]).astype(np.float64))
     assert (np.abs(got[fin] - ref[fin]) <= bound[fin]).all()
+
+
+def _ranges(rng, rows, K):
+    """Rows over K with a random spread of magnitudes, signs and zeros."""
+    kind = rng.integers(4)
+    lo, hi = -45.0 * rng.random(), 12.0 * rng.random()
+    e = np.floor(lo + (hi - lo) * rng.random((rows, K)))
+    if kind == 1:
+        e *= rng.random((1, K)) < 0.5
+    elif kind == 2:
+        e.sort(axis=1)
+    elif kind == 3:
+        e = np.where(rng.random((rows, K)) < 0.02, e + 20.0, lo // 1.0)
+    x = np.ldexp((1.0 + rng.random((rows, K))) * rng.choice([-1.0, 1.0], (rows, K)), e.astype(int))
+    if rng.random() < 0.6:
+        x *= rng.random((rows, K)) < rng.random()
+    if rng.random() < 0.3:
+        x *= rng.random((rows, 1)) < 0.8
+    return x
+
+
+def _meet_zeros(rng, A, B):
+    """Some of the contraction 2^e times as large in A and zero in B."""
+    if rng.random() < 0.5:
+        at = rng.random(A.shape[1]) < 0.3
+        A[:, at] *= 2.0 ** rng.integers(40)
+        B[:, at] = 0.0
+    return A.astype(np.float32), B.astype(np.float32)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_random_ranges(ctx, seed):
+    import torch
+    banner("split random ranges", seed)
+    rng = np.random.default_rng(seed)
+    K, M, N = int(rng.choice([32, 64, 96, 128, 256, 512])), int(rng.integers(1, 300)), 64 * int(rng.integers(1, 4))
+    A, B = _meet_zeros(rng, _ranges(rng, M, K), _ranges(rng, N, K))
+    a, b = A.astype(np.float64), B.astype(np.float64)
+    bound = 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)
+    off = np.array([0, M], np.int32)
+    for trans_b in (0, 1):
+        got = _run(ctx, A, B[None] if trans_b else np.ascontiguousarray(B.T)[None], off, trans_b)
+        assert (np.abs(got - a @ b.T) <= (K + 8) * bound + 1e-45).all(), trans_b
+    rows, P = int(rng.integers(1, 1500)), 64 * int(rng.integers(1, 4))
+    A, B = _meet_zeros(rng, _ranges(rng, P, rows), _ranges(rng, N, rows))
+    got = ctx.grouped_wgrad(torch.from_numpy(np.ascontiguousarray(A.T)).cuda(),
+                            torch.from_numpy(np.ascontiguousarray(B.T)).cuda(),
+                            torch.tensor([0, rows], dtype=torch.int32, device="cuda:0")).cpu().numpy()[0]
+    a, b = A.astype(np.float64), B.astype(np.float64)
+    assert (np.abs(got - a @ b.T) <= (rows + 8) * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T) + 1e-45).all()
